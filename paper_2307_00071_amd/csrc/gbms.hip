@@ -14,6 +14,7 @@
 
 #include "gbms_device.hpp"
 #include "gmm.h"
+#include "readback.hpp"
 
 namespace gmm_host {
 extern thread_local char g_err[512];
@@ -261,8 +262,8 @@ gmm_status run_meanshift(const MsLayout &L, void *ws, hipStream_t s, const float
       HIP_TRY(hipGetLastError());
     }
     unsigned hc[kRoundBatch + 1];
-    HIP_TRY(hipMemcpyAsync(hc, rc, sizeof hc, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    static_assert(kRoundBatch + 1 <= gmm_host::kReadWords, "one read");
+    HIP_TRY(gmm_host::read_words(rc, kRoundBatch + 1, hc, s));
     int r = 1;
     while (r <= kRoundBatch && hc[r] != 0u) ++r;
     if (r <= kRoundBatch) {
@@ -294,8 +295,8 @@ gmm_status run_meanshift(const MsLayout &L, void *ws, hipStream_t s, const float
     HIP_TRY(hipGetLastError());
   }
   MsCounters hcnt;
-  HIP_TRY(hipMemcpyAsync(&hcnt, cnt, sizeof hcnt, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  static_assert(sizeof hcnt % 4 == 0 && sizeof hcnt / 4 <= gmm_host::kReadWords, "one read");
+  HIP_TRY(gmm_host::read_words(cnt, sizeof hcnt / 4, &hcnt, s));
   info->n_seeds = hcnt.ncells;
   info->n_modes = hcnt.kept;
   info->rounds = rounds;

@@ -20,6 +20,7 @@
 #include "small_fit_device.hpp"
 #include "order_device.hpp"
 #include "kinit_device.hpp"
+#include "readback.hpp"
 #include "gmm.h"
 
 // Text of the last host-side error of this thread (shared by every
@@ -922,12 +923,10 @@ gmm_status stage(Run &r, const float *pts, int64_t n, const int32_t *labels,
   return GMM_OK;
 }
 
-gmm_status finish(Run &r, bool sync) {
+gmm_status finish(Run &r, bool sync, bool may_alloc = true) {
   if (!sync) return GMM_OK;
   uint32_t bits = 0;
-  HIP_TRY(hipMemcpyAsync(&bits, at<uint32_t>(r.ws, r.L.status), sizeof bits,
-                         hipMemcpyDeviceToHost, r.s));
-  HIP_TRY(hipStreamSynchronize(r.s));
+  HIP_TRY(gmm_host::read_words(at<uint32_t>(r.ws, r.L.status), 1, &bits, r.s, may_alloc));
   return status_from_bits(bits);
 }
 
@@ -1804,8 +1803,16 @@ gmm_status gmm_workspace_status(const void *ws, void *stream) {
   if (!ws) return fail(GMM_ERR_INVALID_ARG, "ws is NULL");
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint32_t bits = 0;
-  HIP_TRY(hipMemcpyAsync(&bits, ws, sizeof bits, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  // anything but memory of the current device goes by a copy
+  hipPointerAttribute_t pa;
+  int dev = -1;
+  if (hipGetDevice(&dev) == hipSuccess && hipPointerGetAttributes(&pa, ws) == hipSuccess &&
+      pa.type == hipMemoryTypeDevice && pa.device == dev) {
+    HIP_TRY(gmm_host::read_words(ws, 1, &bits, s));
+  } else {
+    (void)hipGetLastError();
+    HIP_TRY(gmm_host::read_words_copy(static_cast<const uint32_t *>(ws), 1, &bits, s));
+  }
   return status_from_bits(bits);
 }
 
@@ -1889,7 +1896,7 @@ gmm_status gmm_fit_noalloc(const float *pts, int64_t n, int32_t k,
   r.sink = nullptr;
   if ((st = enqueue_fit(r, pts, n, init_labels, w, mu, cov, loglik, opts, false)) != GMM_OK)
     return st;
-  return finish(r, true);
+  return finish(r, true, false);
 }
 
 size_t gmm_loglik_workspace_size(int64_t n, int32_t k) {
@@ -2091,9 +2098,7 @@ gmm_status gmm_fit_batched(int32_t B, const float *pts, const int64_t *pt_off,
     return st;
   if (opts->flags & GMM_FLAG_ASYNC) return GMM_OK;
   uint32_t bits = 0;
-  HIP_TRY(hipMemcpyAsync(&bits, at<uint32_t>(ws, bp.status), sizeof bits,
-                         hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(gmm_host::read_words(at<uint32_t>(ws, bp.status), 1, &bits, s));
   return status_from_bits(bits);
 }
 
@@ -2185,8 +2190,7 @@ gmm_status gmm_kmeanspp(const float *pts, int64_t n, int32_t k, const double *u,
     HIP_TRY(hipGetLastError());
   }
   uint32_t bits = 0;
-  HIP_TRY(hipMemcpyAsync(&bits, status, sizeof bits, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(gmm_host::read_words(status, 1, &bits, s));
   return status_from_bits(bits);
 }
 

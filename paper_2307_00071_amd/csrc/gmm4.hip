@@ -16,6 +16,7 @@
 #include "em4_device.hpp"
 #include "gmm.h"
 #include "radix_device.hpp"
+#include "readback.hpp"
 
 namespace gmm_host {
 extern thread_local char g_err[512];
@@ -413,9 +414,7 @@ gmm_status enqueue4(Run4 &r, float *w, float *mu, float *cov, double *loglik,
 gmm_status finish4(Run4 &r, bool sync) {
   if (!sync) return GMM_OK;
   uint32_t bits = 0;
-  HIP_TRY(hipMemcpyAsync(&bits, at<uint32_t>(r.ws, r.L.status), sizeof bits,
-                         hipMemcpyDeviceToHost, r.s));
-  HIP_TRY(hipStreamSynchronize(r.s));
+  HIP_TRY(gmm_host::read_words(at<uint32_t>(r.ws, r.L.status), 1, &bits, r.s));
   return status_from_bits(bits);
 }
 
