@@ -360,37 +360,46 @@ __device__ __forceinline__ void em_update_block(const double *tot, int K, int um
 // Caller-supplied theta_0 (FP32 w, mu, cov) -> FP64 state and E-step block;
 // weights used as given.  One block of kPreThreads threads.
 constexpr int kPreThreads = 1024;
+// One caller component; *bits collects its status.  Returns c_b * log2(e).
+__device__ __forceinline__ double caller_component(int b, const float *__restrict__ w,
+                                                   const float *__restrict__ mu,
+                                                   const float *__restrict__ cov, float *cpar,
+                                                   float4 *shift, double *th64,
+                                                   uint32_t *bits) {
+  double pi = w[b];
+  double m[3] = {mu[3 * b], mu[3 * b + 1], mu[3 * b + 2]};
+  const float *c = cov + 9 * b;
+  double C[6] = {c[0], c[3], c[4], c[6], c[7], c[8]};
+  if (!(pi > 0.0) || !isfinite(pi) || !isfinite(m[0]) || !isfinite(m[1]) ||
+      !isfinite(m[2])) {
+    *bits |= kStBadArg;
+    pi = 1.0;
+  }
+  const double cc = component_terms(b, pi, m, C, 0.0, cpar, shift, th64);
+  if (!isfinite(cc)) *bits |= kStNotSpd;
+  return cc;
+}
+
 __global__ __launch_bounds__(kPreThreads) void precompute_kernel(
     const float *__restrict__ w, const float *__restrict__ mu,
     const float *__restrict__ cov, int K, float *cpar, float4 *shift,
     double *th64, uint32_t *status) {
   __shared__ double scratch[kPreThreads];
   __shared__ double sC[GMM_MAX_K];
-  for (int b = threadIdx.x; b < K; b += kPreThreads) {
-    double pi = w[b];
-    double m[3] = {mu[3 * b], mu[3 * b + 1], mu[3 * b + 2]};
-    const float *c = cov + 9 * b;
-    double C[6] = {c[0], c[3], c[4], c[6], c[7], c[8]};
-    if (!(pi > 0.0) || !isfinite(pi) || !isfinite(m[0]) || !isfinite(m[1]) ||
-        !isfinite(m[2])) {
-      set_status(status, kStBadArg);
-      pi = 1.0;
-    }
-    const double cc = component_terms(b, pi, m, C, 0.0, cpar, shift, th64);
-    if (!isfinite(cc)) set_status(status, kStNotSpd);
-    sC[b] = cc;
-  }
+  uint32_t bits = 0;
+  for (int b = threadIdx.x; b < K; b += kPreThreads)
+    sC[b] = caller_component(b, w, mu, cov, cpar, shift, th64, &bits);
+  if (bits) set_status(status, bits);
   apply_bound<kPreThreads>(K, sC, cpar, scratch);
 }
 
 // ------------------------------------------------------------ stage kernel
 // AoS N x 3 (caller) -> float4 (x, y, z, tag) padded to a tile multiple.
 // tag (int bits) = label in label mode, 0 for a real point otherwise, and -1
-// for padding.  With a pose, y = R x + t in FP32.
+// for padding.
 __global__ void stage_kernel(const float *__restrict__ pts, int64_t n,
                              int64_t npad, const int32_t *__restrict__ labels,
-                             int K, const float *__restrict__ Rt,
-                             float4 *__restrict__ out, uint32_t *status) {
+                             int K, float4 *__restrict__ out, uint32_t *status) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= npad) return;
   if (i >= n) {
@@ -401,12 +410,6 @@ __global__ void stage_kernel(const float *__restrict__ pts, int64_t n,
   if (!isfinite(x) || !isfinite(y) || !isfinite(z)) {
     set_status(status, kStNonFinite);
     x = y = z = 0.0f;
-  }
-  if (Rt) {
-    float u = fmaf(Rt[0], x, fmaf(Rt[1], y, fmaf(Rt[2], z, Rt[9])));
-    float v = fmaf(Rt[3], x, fmaf(Rt[4], y, fmaf(Rt[5], z, Rt[10])));
-    float w = fmaf(Rt[6], x, fmaf(Rt[7], y, fmaf(Rt[8], z, Rt[11])));
-    x = u; y = v; z = w;
   }
   int tag = 0;
   if (labels) {
@@ -419,13 +422,12 @@ __global__ void stage_kernel(const float *__restrict__ pts, int64_t n,
   out[i] = make_float4(x, y, z, __int_as_float(tag));
 }
 
-// --------------------------------------------------------------- pose kernel
+// ---------------------------------------------------------------------- pose
 // R = exp([omega]_x) (Rodrigues), the SO(3) left Jacobian J, both FP64, and
 // an FP32 copy (R row-major, t) for the staging kernel.
 // pose64: [0..8] R, [9..11] t, [12..20] J.
-__global__ void pose_kernel(const float *__restrict__ pose6, double *pose64,
-                            float *Rt32) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ inline void pose_terms(const float *__restrict__ pose6, double *pose64,
+                                  float *Rt32) {
   double w[3] = {pose6[0], pose6[1], pose6[2]};
   double th2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
   double th = sqrt(th2), a, bb, e;
@@ -812,6 +814,16 @@ struct CullShape {
 // parameters in registers and the shifts are read from global memory),
 // FP64 sums, masks, fallback (max, sum) per point, wL, partial normalisers,
 // the active list and its length.
+// The log-likelihood pass has no E rows, Xs, shifts, sums and fallback
+// entries, its cull parameters are in registers, and it holds the far
+// points' component words instead.
+template <int BLOCK, int T>
+__host__ __device__ constexpr size_t lik_lds_bytes(int K) {
+  return 32 * sizeof(uint64_t) + (size_t)(T / 64) * sizeof(uint64_t) +
+         (size_t)(BLOCK / 64) * sizeof(double) + (size_t)BLOCK * sizeof(float) +
+         (size_t)(T / 64) * 64 * sizeof(uint32_t) + (size_t)2 * K * sizeof(uint16_t) + 16;
+}
+
 template <int BLOCK, int T, int TRIP, int SCAP, bool CPR = false>
 __host__ __device__ constexpr size_t cull_lds_bytes(int K) {
   using S = CullShape<BLOCK, T, TRIP, SCAP>;
@@ -823,6 +835,40 @@ __host__ __device__ constexpr size_t cull_lds_bytes(int K) {
          (size_t)S::W * sizeof(uint64_t) + (size_t)S::NW * sizeof(double) +
          (size_t)T * sizeof(float2) + (size_t)S::R * T * sizeof(float) +
          (size_t)2 * K * sizeof(uint16_t) + 16;
+}
+
+// Bounds of a tile from the extremes of its points, widened for the rounding
+// of the centre: a sphere (centre, radius; radius < 0 for a tile of padding
+// only: lo > hi), or a box (centre, -1 for padding only), (half extents).
+__device__ __forceinline__ float4 tile_sphere(float lo0, float lo1, float lo2, float hi0,
+                                              float hi1, float hi2) {
+  if (!(lo0 <= hi0)) return make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+  const float c0 = 0.5f * (lo0 + hi0), c1 = 0.5f * (lo1 + hi1),
+              c2 = 0.5f * (lo2 + hi2);
+  const float e0 = hi0 - lo0, e1 = hi1 - lo1, e2 = hi2 - lo2;
+  // half diagonal, widened for the rounding of the centre and the norm
+  const float scale = fmaxf(fmaxf(fabsf(c0), fabsf(c1)), fabsf(c2)) + 1.0f;
+  const float r = 0.5f * sqrtf(e0 * e0 + e1 * e1 + e2 * e2) * (1.0f + 1e-5f) +
+                  1e-5f * scale;
+  return make_float4(c0, c1, c2, r);
+}
+
+struct TileBox {
+  float4 c, h;
+};
+__device__ __forceinline__ TileBox tile_box(float lo0, float lo1, float lo2, float hi0,
+                                            float hi1, float hi2) {
+  TileBox t;
+  t.c = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+  t.h = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (!(lo0 <= hi0)) return t;
+  t.c = make_float4(0.5f * (lo0 + hi0), 0.5f * (lo1 + hi1), 0.5f * (lo2 + hi2), 1.0f);
+  const float pad =
+      1e-5f * (fmaxf(fmaxf(fabsf(t.c.x), fabsf(t.c.y)), fabsf(t.c.z)) + 1.0f);
+  t.h.x = 0.5f * (hi0 - lo0) * (1.0f + 1e-5f) + pad;
+  t.h.y = 0.5f * (hi1 - lo1) * (1.0f + 1e-5f) + pad;
+  t.h.z = 0.5f * (hi2 - lo2) * (1.0f + 1e-5f) + pad;
+  return t;
 }
 
 // Bounding sphere of every tile of tpts staged points: (centre, radius),
@@ -859,18 +905,7 @@ __global__ __launch_bounds__(256) void tile_sphere_kernel(
     lo0 = fminf(lo0, sh[v][0]); lo1 = fminf(lo1, sh[v][1]); lo2 = fminf(lo2, sh[v][2]);
     hi0 = fmaxf(hi0, sh[v][3]); hi1 = fmaxf(hi1, sh[v][4]); hi2 = fmaxf(hi2, sh[v][5]);
   }
-  if (!(lo0 <= hi0)) {
-    sph[t] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
-    return;
-  }
-  const float c0 = 0.5f * (lo0 + hi0), c1 = 0.5f * (lo1 + hi1),
-              c2 = 0.5f * (lo2 + hi2);
-  const float e0 = hi0 - lo0, e1 = hi1 - lo1, e2 = hi2 - lo2;
-  // half diagonal, widened for the rounding of the centre and the norm
-  const float scale = fmaxf(fmaxf(fabsf(c0), fabsf(c1)), fabsf(c2)) + 1.0f;
-  const float r = 0.5f * sqrtf(e0 * e0 + e1 * e1 + e2 * e2) * (1.0f + 1e-5f) +
-                  1e-5f * scale;
-  sph[t] = make_float4(c0, c1, c2, r);
+  sph[t] = tile_sphere(lo0, lo1, lo2, hi0, hi1, hi2);
 }
 
 // v + the value of another lane (DPP, within rows of 16 lanes):
@@ -970,6 +1005,26 @@ __device__ __forceinline__ bool cull_test(float4 u, float4 v, float4 z, float4 s
   return fmaf(-bnd, bnd, u.w) >= kCullLog2;
 }
 
+// The cull test with a box: each coordinate of P'(x - mu) stays within the
+// box's reach of its value at the centre, |P'|h, so its square is at least
+// max(0, |z_i| - (|P'| h)_i)^2.  Tighter than the sphere where the points of
+// a tile lie along a line or in a plane.
+__device__ __forceinline__ bool box_test(const CullPar &p, const TileBox &t) {
+  const float d0 = t.c.x - p.u.x, d1 = t.c.y - p.u.y, d2 = t.c.z - p.u.z;
+  const float z0 = p.v.x * d0;
+  const float z1 = fmaf(p.v.y, d0, p.v.z * d1);
+  const float z2 = fmaf(p.v.w, d0, fmaf(p.z.x, d1, p.z.y * d2));
+  const float r0 = fabsf(p.v.x) * t.h.x;
+  const float r1 = fmaf(fabsf(p.v.y), t.h.x, fabsf(p.v.z) * t.h.y);
+  const float r2 = fmaf(fabsf(p.v.w), t.h.x, fmaf(fabsf(p.z.x), t.h.y, fabsf(p.z.y) * t.h.z));
+  const float b0 = fmaxf(fabsf(z0) - r0, 0.0f), b1 = fmaxf(fabsf(z1) - r1, 0.0f),
+              b2 = fmaxf(fabsf(z2) - r2, 0.0f);
+  return p.u.w - fmaf(b0, b0, fmaf(b1, b1, b2 * b2)) >= kCullLog2;
+}
+__device__ __forceinline__ uint64_t box_ballot(const CullPar &p, const TileBox &t) {
+  return __ballot(t.c.w >= 0.0f && box_test(p, t));
+}
+
 // The wave's ballot of the cull test, this lane's component in registers
 // or (3 float4) in LDS.
 __device__ __forceinline__ uint64_t cull_ballot(const CullPar &cp, float4 sp) {
@@ -1002,6 +1057,7 @@ struct CullLds {
   float *reds;       // R x T
   uint16_t *list;    // 2 x K component indices (K <= 1024)
   int *nact_s;       // 2
+  uint32_t *cand;    // LIK: W x 64 words of 16 components
 };
 
 template <int BLOCK, int T, int TRIP, int SCAP, bool CPR>
@@ -1022,6 +1078,20 @@ __device__ __forceinline__ CullLds cull_carve(unsigned char *smem, int K) {
   L.reds = reinterpret_cast<float *>(L.fbv + T);
   L.list = reinterpret_cast<uint16_t *>(L.reds + S::R * T);
   L.nact_s = reinterpret_cast<int *>(L.list + 2 * K);  // 2K uint16: 4-byte aligned
+  return L;
+}
+
+template <int BLOCK, int T>
+__device__ __forceinline__ CullLds lik_carve(unsigned char *smem, int K) {
+  constexpr int W = T / 64, NW = BLOCK / 64;
+  CullLds L = {};
+  L.masks = reinterpret_cast<uint64_t *>(smem);
+  L.fbmask = L.masks + 32;
+  L.wL = reinterpret_cast<double *>(L.fbmask + W);
+  L.reds = reinterpret_cast<float *>(L.wL + NW);      // R x T = BLOCK
+  L.cand = reinterpret_cast<uint32_t *>(L.reds + BLOCK);
+  L.list = reinterpret_cast<uint16_t *>(L.cand + W * 64);
+  L.nact_s = reinterpret_cast<int *>(L.list + 2 * K);
   return L;
 }
 
@@ -1075,8 +1145,9 @@ __device__ __forceinline__ TilePre tile_pre(const float4 *__restrict__ pts,
 
 // The tiles first, first + stride, ... < end of one frame: cull, E-phase,
 // normaliser, M-phase into L.acc; lse sums into Lacc, active pairs into
-// npairs (thread 0).
-template <int BLOCK, int T, int TRIP, int SCAP, bool CPR, bool LAB, bool MEANS = false>
+// npairs (thread 0).  LIK: the log-likelihood alone, no E rows and no M-phase.
+template <int BLOCK, int T, int TRIP, int SCAP, bool CPR, bool LAB, bool MEANS = false,
+          bool LIK = false>
 __device__ __forceinline__ void cull_tiles(
     const CullLds &L, const float4 *__restrict__ pts, const float4 *__restrict__ sph,
     const float *__restrict__ cpar, const float4 *__restrict__ shift, int K, int mode,
@@ -1208,7 +1279,8 @@ __device__ __forceinline__ void cull_tiles(
           }
 #pragma unroll
           for (int u = 0; u < EU; ++u) s += e[u];
-          if (sl + (EU - 1) * R < SCAP) {
+          if constexpr (LIK) {
+          } else if (sl + (EU - 1) * R < SCAP) {
 #pragma unroll
             for (int u = 0; u < EU; ++u) E[(sl + u * R) * RS + tx] = e[u];
           } else {
@@ -1222,7 +1294,7 @@ __device__ __forceinline__ void cull_tiles(
           const float e0 = __builtin_amdgcn_exp2f(
               comp_logterm(cpar + (size_t)b0 * kParStride, x.x, x.y, x.z));
           s += e0;
-          if (sl < SCAP) E[sl * RS + tx] = e0;
+          if (!LIK && sl < SCAP) E[sl * RS + tx] = e0;
         }
       }
       reds[rr * T + t] = s;
@@ -1241,7 +1313,7 @@ __device__ __forceinline__ void cull_tiles(
         for (int j = 1; j < R; ++j) st += reds[j * T + t];
         const bool fb = valid && !(st >= 0x1p-100f);
         float mref = 0.0f;
-        if (fb) {
+        if (!LIK && fb) {
           // far from every component: own maximum over all K (as the dense
           // kernel's fallback); the point joins the statistics afterwards
           float mx = -INFINITY;
@@ -1254,11 +1326,12 @@ __device__ __forceinline__ void cull_tiles(
           mref = mx;
           fbv[t] = make_float2(mx, st);
         }
-        Xs[tx] = make_float4(x.x, x.y, x.z,
-                             (valid && !fb) ? __builtin_amdgcn_rcpf(st) : 0.0f);
+        if constexpr (!LIK)
+          Xs[tx] = make_float4(x.x, x.y, x.z,
+                               (valid && !fb) ? __builtin_amdgcn_rcpf(st) : 0.0f);
         const uint64_t fm = __ballot(fb);
         if (lane == 0) fbmask[pg] = fm;
-        if (valid) {
+        if (valid && !(LIK && fb)) {
           const double lse = (Cb + (double)mref + (double)__builtin_amdgcn_logf(st)) * kLn2;
           Lacc += lse;
           if (lse_out) lse_out[(size_t)tile * T + t] = (float)lse;
@@ -1271,7 +1344,7 @@ __device__ __forceinline__ void cull_tiles(
 
     // ---- M-phase over the active list, SCAP slots at a time
     if (tid == 0) npairs += (unsigned)nact;
-    if (mode != kSoftLogLik) {
+    if (!LIK && mode != kSoftLogLik) {
       const int q = tid % P;
       for (int c0 = 0; c0 < nact; c0 += SCAP) {
         const int nloc = min(SCAP, nact - c0);
@@ -1345,7 +1418,55 @@ __device__ __forceinline__ void cull_tiles(
     bool anyfb = false;
 #pragma unroll
     for (int g2 = 0; g2 < W; ++g2) anyfb = anyfb || fbmask[g2] != 0;
-    if (mode != kSoftLogLik && anyfb) {
+    if constexpr (LIK) {
+    // the maximum over all K components and the sum of 2^(l' - max), lanes =
+    // points (far points come in clusters), the R waves of a point group
+    // sharing the components: maxima of contiguous ranges; the components
+    // that are not zero for every far point, in words of 16; the sum by the
+    // first wave over those alone, in component order, so that its float32
+    // rounding is that of a loop over all of them (2 K evaluations in one
+    // wave before).
+    if (anyfb) {
+      const bool fb = (fbmask[pg] >> lane) & 1ull;
+      float mx = -INFINITY;
+      for (int b = (rr * K) / R; b < ((rr + 1) * K) / R; ++b)
+        mx = fmaxf(mx, comp_logterm(cpar + (size_t)b * kParStride, x.x, x.y, x.z));
+      reds[rr * T + t] = mx;
+      __syncthreads();
+      mx = reds[t];
+#pragma unroll
+      for (int j = 1; j < R; ++j) mx = fmaxf(mx, reds[j * T + t]);
+      const int nword = (K + 15) >> 4;
+      uint32_t *cand = L.cand + pg * 64;   // K <= 1024
+      for (int c = rr; c < nword; c += R) {
+        uint32_t cm = 0;
+        for (int i = 0; i < min(16, K - 16 * c); ++i) {
+          const float d =
+              comp_logterm(cpar + (size_t)(16 * c + i) * kParStride, x.x, x.y, x.z) - mx;
+          if (__ballot(fb && !(d <= -150.0f))) cm |= 1u << i;
+        }
+        if (lane == 0) cand[c] = cm;
+      }
+      __syncthreads();
+      if (rr == 0) {
+        float st = 0.0f;
+        for (int c = 0; c < nword; ++c) {
+          uint32_t cm = __builtin_amdgcn_readfirstlane(cand[c]);
+          while (cm) {
+            const int b = 16 * c + __builtin_ctz(cm);
+            cm &= cm - 1;
+            st += __builtin_amdgcn_exp2f(
+                comp_logterm(cpar + (size_t)b * kParStride, x.x, x.y, x.z) - mx);
+          }
+        }
+        if (fb) {
+          const double lse = (Cb + (double)mx + (double)__builtin_amdgcn_logf(st)) * kLn2;
+          Lacc += lse;
+          if (lse_out) lse_out[(size_t)tile * T + t] = (float)lse;
+        }
+      }
+    }
+    } else if (mode != kSoftLogLik && anyfb) {
       __syncthreads();
       if (w == 0) {
         for (int g2 = 0; g2 < W; ++g2) {
@@ -1443,6 +1564,30 @@ __attribute__((amdgpu_waves_per_eu(GMM_CULL_WPE, 8))) void em_cull_kernel(
   if (threadIdx.x == 0 && a.pairs) atomicAdd(a.pairs, npairs);
 }
 
+// The log-likelihood pass: one value per block, the last column of its row.
+// As a mode of em_cull_kernel it held the M-phase's LDS and registers (two
+// or three blocks per CU); without them, and with the far points shared by
+// the waves, N = 100,000, K = 200 (14 % far points) takes 38 us instead of
+// 64, N = 5,000, K = 64 10.8 us instead of 17.4.
+template <int BLOCK, int T>
+__global__ __launch_bounds__(BLOCK) void em_lik_kernel(
+    const float4 *__restrict__ pts, const float4 *__restrict__ sph,
+    const float *__restrict__ cpar, double *__restrict__ part, float *__restrict__ lse_out,
+    TileArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int TRIP = T / 8, SCAP = 1;   // not used by this pass
+  const TilePre pre =
+      tile_pre<BLOCK, T, TRIP, SCAP, false>(pts, sph, blockIdx.x, a.ntiles, gridDim.x);
+  const CullLds L = lik_carve<BLOCK, T>(smem, a.K);
+  double Lacc = 0.0;
+  unsigned long long npairs = 0;
+  cull_tiles<BLOCK, T, TRIP, SCAP, true, false, false, true>(
+      L, pts, sph, cpar, nullptr, a.K, kSoftLogLik, blockIdx.x, a.ntiles, gridDim.x, lse_out,
+      Lacc, npairs, pre);
+  cull_end<BLOCK>(L, part + (size_t)blockIdx.x * a.ncols, a.K, kSoftLogLik, Lacc);
+  if (threadIdx.x == 0 && a.pairs) atomicAdd(a.pairs, npairs);
+}
+
 // ------------------------------------------------------ reduction kernels
 // Two fence-free launches after each tile pass:
 //  reduce_rows_kernel  red2[y][c] = sum of part[r][c] over the y-th of
@@ -1456,8 +1601,7 @@ __attribute__((amdgpu_waves_per_eu(GMM_CULL_WPE, 8))) void em_cull_kernel(
 // update block then has all of a thread's loads (4 columns x 4 rows) in
 // flight at once.  Measured per 100-iteration fit at K = 100: 16 chunks
 // 0.28 ms slower, 2 or 1 chunk 0.14 / 0.43 ms slower, 256-thread reduce
-// blocks 0.07 ms slower.  The backward pass reduces into kRedChunks chunks.
-constexpr int kRedChunks = 16;
+// blocks 0.07 ms slower.
 constexpr int kRedChunksFit = 4;
 constexpr int kUpdThreads = 1024;
 
@@ -2240,90 +2384,6 @@ __host__ __device__ constexpr size_t bwd_lds_bytes(int K) {
   using S = TileShape<BLOCK, T>;
   return tile_lds_bytes_e<BLOCK, T>(K, K) + S::TS * sizeof(float4) +
          4 * (size_t)S::G * T * sizeof(float) + 7 * (BLOCK / 64) * sizeof(double);
-}
-
-// Final step of the backward (one block): from the reduced columns and the
-// FP32 mixture (Sigma^-1 = P^T P from an FP64 Cholesky),
-//   dL/dpi_b = N_b / pi_b,  dL/dmu_b = Sigma^-1 A_b,
-//   dL/dSigma_b = 1/2 Sigma^-1 B_b Sigma^-1 - 1/2 N_b Sigma^-1,
-//   dL/dt = sum g,  dL/domega = J_l^T sum (y - t) x g,
-// all times grad_L.
-__global__ __launch_bounds__(256) void bwd_finish_kernel(
-    const double *__restrict__ red2, int ncols, int K,
-    const float *__restrict__ w, const float *__restrict__ cov,
-    const double *__restrict__ pose64, const double *__restrict__ grad_L,
-    float *g_pose6, float *g_w, float *g_mu, float *g_cov, uint32_t *status) {
-  const double gl = grad_L ? grad_L[0] : 1.0;
-  auto col = [&](int c) {
-    double t = 0.0;
-#pragma unroll
-    for (int y = 0; y < kRedChunks; ++y) t += red2[(size_t)y * ncols + c];
-    return t;
-  };
-  for (int b = threadIdx.x; b < K; b += blockDim.x) {
-    const double N = col(b);
-    const double A[3] = {col(K + b), col(2 * K + b), col(3 * K + b)};
-    double Bl[6];
-    for (int j = 0; j < 6; ++j) Bl[j] = col((4 + j) * K + b);
-    const float *c = cov + 9 * b;
-    const double C[6] = {c[0], c[3], c[4], c[6], c[7], c[8]};
-    double L[6], P[6];
-    if (!chol3(C, L)) {
-      // no gradient exists: the component's outputs are NaN, not stale memory
-      set_status(status, kStNotSpd);
-      const float nan = __builtin_nanf("");
-      if (g_w) g_w[b] = nan;
-      if (g_mu)
-        for (int i = 0; i < 3; ++i) g_mu[3 * b + i] = nan;
-      if (g_cov)
-        for (int i = 0; i < 9; ++i) g_cov[9 * b + i] = nan;
-      continue;
-    }
-    tri_inv3(L, P);
-    // Sigma^-1 = P^T P (full symmetric)
-    const double Pm[9] = {P[0], 0.0, 0.0, P[1], P[2], 0.0, P[3], P[4], P[5]};
-    double Si[9];
-    for (int i = 0; i < 3; ++i)
-      for (int j = 0; j < 3; ++j) {
-        double v = 0.0;
-        for (int k = 0; k < 3; ++k) v += Pm[k * 3 + i] * Pm[k * 3 + j];
-        Si[i * 3 + j] = v;
-      }
-    const double B[9] = {Bl[0], Bl[1], Bl[3], Bl[1], Bl[2], Bl[4], Bl[3], Bl[4], Bl[5]};
-    if (g_w) g_w[b] = (float)(gl * N / (double)w[b]);
-    if (g_mu)
-      for (int i = 0; i < 3; ++i)
-        g_mu[3 * b + i] = (float)(gl * (Si[i * 3] * A[0] + Si[i * 3 + 1] * A[1] + Si[i * 3 + 2] * A[2]));
-    if (g_cov) {
-      double T1[9];
-      for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-          double v = 0.0;
-          for (int k = 0; k < 3; ++k) v += Si[i * 3 + k] * B[k * 3 + j];
-          T1[i * 3 + j] = v;
-        }
-      for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-          double v = 0.0;
-          for (int k = 0; k < 3; ++k) v += T1[i * 3 + k] * Si[k * 3 + j];
-          g_cov[9 * b + i * 3 + j] = (float)(gl * (0.5 * v - 0.5 * N * Si[i * 3 + j]));
-        }
-    }
-  }
-  if (threadIdx.x == 0 && g_pose6) {
-    const int c0 = kNStat * K + 1;
-    const double gs[3] = {col(c0), col(c0 + 1), col(c0 + 2)};
-    const double h[3] = {col(c0 + 3), col(c0 + 4), col(c0 + 5)};
-    double J[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
-    if (pose64)
-      for (int i = 0; i < 9; ++i) J[i] = pose64[12 + i];
-    for (int i = 0; i < 3; ++i) {
-      g_pose6[i] = (float)(gl * (J[i] * h[0] + J[3 + i] * h[1] + J[6 + i] * h[2]));
-      g_pose6[3 + i] = (float)(gl * gs[i]);
-    }
-    if (!isfinite(gs[0] + gs[1] + gs[2] + h[0] + h[1] + h[2]))
-      set_status(status, kStNonFinite);
-  }
 }
 
 }  // namespace gmm_dev

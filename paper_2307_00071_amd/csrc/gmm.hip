@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "em_device.hpp"
+#include "lik_device.hpp"
 #include "small_fit_device.hpp"
 #include "order_device.hpp"
 #include "kinit_device.hpp"
@@ -283,6 +284,35 @@ bool make_bwd_cfg(int K, int64_t n, BwdCfg *out) {
   return true;
 }
 
+// Launch configuration of the culled backward kernel (one wave per
+// 64-component chunk, so K <= 512).
+struct BwdCullCfg {
+  int grid = 0;
+  size_t lds = 0;
+};
+constexpr int kBwdCullRows = 64;   // E rows kept
+
+bool pick_bwd_cull_cfg(int K, int64_t n, BwdCullCfg *out) {
+  const char *off = getenv("GMM_CULL");
+  if (off && off[0] == '0') return false;
+  DevInfo di = dev_info();
+  if (di.cus <= 0 || K > kBwdCullBlock) return false;
+  const size_t lds = bwd_cull_lds_bytes<kBwdCullRows>(K);
+  if (lds > (di.lds_max ? di.lds_max : 65536)) return false;
+  const void *fn = reinterpret_cast<const void *>(&em_bwd_cull_kernel<kBwdCullRows>);
+  if (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds) != hipSuccess)
+    return false;
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBwdCullBlock, lds) !=
+          hipSuccess || per_cu <= 0)
+    return false;
+  const int64_t ntiles = (n + kBwdCullT - 1) / kBwdCullT;
+  out->grid = (int)std::min<int64_t>(ntiles, (int64_t)di.cus * per_cu);
+  out->lds = lds;
+  return true;
+}
+
 bool pick_bwd_cfg(int K, int64_t n, BwdCfg *out) {
   if (K <= 128 && make_bwd_cfg<512, 64>(K, n, out)) return true;
   return make_bwd_cfg<1024, 64>(K, n, out);
@@ -421,7 +451,19 @@ struct CullCfg {
   Launch launch = nullptr;        // soft passes
   Launch launch_lab = nullptr;    // label passes
   Launch launch_means = nullptr;  // soft passes for N and S1 only
+  // log-likelihood passes: their own kernel, whose blocks need less LDS
+  int grid_lik = 0;
+  size_t lds_lik = 0;
+  Launch launch_lik = nullptr;
 };
+
+template <int BLOCK, int T>
+void launch_lik(const CullCfg &c, hipStream_t s, const float4 *pts, const float4 *sph,
+                const float *cpar, const float4 *, double *part, float *lse,
+                const TileArgs &a) {
+  hipLaunchKernelGGL((em_lik_kernel<BLOCK, T>), dim3(c.grid_lik), dim3(BLOCK), c.lds_lik, s,
+                     pts, sph, cpar, part, lse, a);
+}
 
 template <int BLOCK, int T, int TRIP, int SCAP, bool CPR, bool LAB, bool MEANS>
 void launch_cull(const CullCfg &c, hipStream_t s, const float4 *pts,
@@ -466,6 +508,17 @@ bool make_cull_cfg(int K, int64_t n, CullCfg *out) {
   out->launch = &launch_cull<BLOCK, T, TRIP, SCAP, CPR, false, false>;
   out->launch_lab = &launch_cull<BLOCK, T, TRIP, SCAP, CPR, true, false>;
   out->launch_means = &launch_cull<BLOCK, T, TRIP, SCAP, CPR, false, true>;
+  const void *fk = reinterpret_cast<const void *>(&em_lik_kernel<BLOCK, T>);
+  out->lds_lik = lik_lds_bytes<BLOCK, T>(K);
+  if (out->lds_lik > 65536 &&
+      hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out->lds_lik) !=
+          hipSuccess)
+    return false;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fk, BLOCK, out->lds_lik) !=
+          hipSuccess || per_cu <= 0)
+    return false;
+  out->grid_lik = (int)std::min<int64_t>(ntiles, (int64_t)di.cus * per_cu);
+  out->launch_lik = &launch_lik<BLOCK, T>;
   return true;
 }
 
@@ -547,6 +600,7 @@ struct WsLayout {
   // spatial ordering (fits): unsorted staging, keys/indices, digit counts
   size_t raw4 = 0, keys[2] = {0, 0}, vals[2] = {0, 0}, hist = 0, dtot = 0, box6 = 0;
   int sort_blocks = 0;
+  size_t flags = 0;   // registration calls: a status word per setup block
   int64_t npad;
   int ncols, nslots;
 };
@@ -555,7 +609,7 @@ struct WsLayout {
 constexpr int64_t kSortMaxN = (int64_t)1 << 30;
 
 WsLayout ws_layout(int64_t n, int K, const TileCfg &c, int extra_cols = 0,
-                   int grid_override = 0, bool with_sort = false) {
+                   int grid_override = 0, bool with_sort = false, bool lik = false) {
   WsLayout L{};
   size_t o = 0;
   L.ncols = kNStat * K + 1 + extra_cols;
@@ -572,10 +626,14 @@ WsLayout ws_layout(int64_t n, int K, const TileCfg &c, int extra_cols = 0,
     L.shift[i] = o; o = align256(o + (size_t)K * sizeof(float4));
   }
   L.th64 = o; o = align256(o + (size_t)K * kTh64Stride * sizeof(double));
-  L.red = o; o = align256(o + (size_t)kRedChunks * L.ncols * sizeof(double));
+  L.red = o; o = align256(o + (size_t)kRedChunksFit * L.ncols * sizeof(double));
   L.part = o; o = align256(o + (size_t)L.nslots * L.ncols * sizeof(double));
   L.pts4 = o; o = align256(o + (size_t)L.npad * sizeof(float4));
-  L.tsph = o; o = align256(o + (size_t)(L.npad / 64) * sizeof(float4));
+  // tile spheres; the backward pass keeps a box (two float4) per tile
+  L.tsph = o; o = align256(o + (size_t)(L.npad / 64) * (lik ? 2 : 1) * sizeof(float4));
+  if (lik) {
+    L.flags = o; o = align256(o + (size_t)(kLikMaxBlocks + 1) * sizeof(uint32_t));
+  }
   if (with_sort && L.npad <= kSortMaxN) {
     L.sort_blocks = (int)((L.npad + kSortChunk - 1) / kSortChunk);
     L.raw4 = o; o = align256(o + (size_t)L.npad * sizeof(float4));
@@ -710,10 +768,10 @@ gmm_status autotune(Run &r, int64_t n) {
   return GMM_OK;
 }
 
-// One pass: the tile kernel, then the reduction and the M-step update.
-gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot,
-                    float *lse, float *out_w = nullptr, float *out_mu = nullptr,
-                    float *out_cov = nullptr) {
+// The tile kernel of one pass (repeated and timed when profiling); *rows =
+// the partial rows it writes.
+gmm_status run_tiles(Run &r, int mode, int umode, float *lse, const unsigned *conv, int cmaj,
+                     int *rows) {
   const WsLayout &L = r.L;
   const bool cull = r.cull;  // label passes too: a tile's components are its labels
   TileArgs a;
@@ -723,17 +781,11 @@ gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot
   a.P = r.c.P;
   a.mode = mode;
   a.ncols = L.ncols;
-  // with a tolerance, the soft passes check the converged flag: words 0
-  // and 1 of the counter buffer take turns as the current and the next
-  // state (a full M-step writes the next), the double at word 2 is L_prev
-  unsigned *cbase = at<unsigned>(r.ws, L.counter);
-  unsigned *conv = (r.tol_abs > 0.0 && mode == kSoftStats) ? cbase + r.conv_par : nullptr;
-  unsigned *conv_next = (conv && umode == kUpdFull) ? cbase + (1 - r.conv_par) : nullptr;
-  double *Lprev = conv ? reinterpret_cast<double *>(cbase + 2) : nullptr;
   a.conv = conv;
-  const int rows = cull ? r.cc.grid : r.c.grid;  // partial rows written
-  const bool fuse = r.fused && reg > 0.0;
-  a.cmaj = fuse ? 1 : 0;   // the fused reduction reads a component's sums together
+  a.cmaj = cmaj;
+  // the workspace holds nslots rows
+  r.cc.grid_lik = std::min(r.cc.grid_lik, L.nslots);
+  *rows = !cull ? r.c.grid : mode == kSoftLogLik ? r.cc.grid_lik : r.cc.grid;
   EventPair pp;
   const bool timed = r.sink && (mode == kSoftStats || r.time_loglik);
   if (timed) {
@@ -751,6 +803,7 @@ gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot
   for (int rep = 0; rep < (timed ? g_prof.reps : 1); ++rep) {
     if (cull)
       (mode == kLabels                                  ? r.cc.launch_lab
+       : mode == kSoftLogLik                            ? r.cc.launch_lik
        : mode == kSoftStats && umode == kUpdMeanOnly ? r.cc.launch_means
                                                      : r.cc.launch)(
                   r.cc, r.s, at<float4>(r.ws, L.pts4), at<float4>(r.ws, L.tsph),
@@ -762,6 +815,26 @@ gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot
     HIP_TRY(hipGetLastError());
   }
   if (timed) HIP_TRY(hipEventRecord(pp.b, r.s));
+  return GMM_OK;
+}
+
+// One pass: the tile kernel, then the reduction and the M-step update.
+gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot,
+                    float *out_w = nullptr, float *out_mu = nullptr,
+                    float *out_cov = nullptr) {
+  const WsLayout &L = r.L;
+  // with a tolerance, the soft passes check the converged flag: words 0
+  // and 1 of the counter buffer take turns as the current and the next
+  // state (a full M-step writes the next), the double at word 2 is L_prev
+  unsigned *cbase = at<unsigned>(r.ws, L.counter);
+  unsigned *conv = (r.tol_abs > 0.0 && mode == kSoftStats) ? cbase + r.conv_par : nullptr;
+  unsigned *conv_next = (conv && umode == kUpdFull) ? cbase + (1 - r.conv_par) : nullptr;
+  double *Lprev = conv ? reinterpret_cast<double *>(cbase + 2) : nullptr;
+  // the fused reduction reads a component's sums together
+  const bool fuse = r.fused && reg > 0.0;
+  int rows = 0;
+  gmm_status st = run_tiles(r, mode, umode, nullptr, conv, fuse ? 1 : 0, &rows);
+  if (st != GMM_OK) return st;
   const int nxt = 1 - r.cur;
   if (conv_next) r.conv_par = 1 - r.conv_par;
   if (fuse) {
@@ -900,12 +973,11 @@ bool sort_enabled() {
   return !(e && e[0] == '0');
 }
 
-gmm_status stage(Run &r, const float *pts, int64_t n, const int32_t *labels,
-                 const float *Rt, bool sort = false) {
+gmm_status stage(Run &r, const float *pts, int64_t n, const int32_t *labels, bool sort) {
   const int64_t nb = (r.L.npad + 255) / 256;
   sort = sort && r.cull && r.L.sort_blocks > 0;
   hipLaunchKernelGGL(stage_kernel, dim3((unsigned)nb), dim3(256), 0, r.s, pts,
-                     n, r.L.npad, labels, r.K, Rt,
+                     n, r.L.npad, labels, r.K,
                      at<float4>(r.ws, sort ? r.L.raw4 : r.L.pts4),
                      at<uint32_t>(r.ws, r.L.status));
   HIP_TRY(hipGetLastError());
@@ -920,6 +992,30 @@ gmm_status stage(Run &r, const float *pts, int64_t n, const int32_t *labels,
                        at<float4>(r.ws, r.L.tsph));
     HIP_TRY(hipGetLastError());
   }
+  return GMM_OK;
+}
+
+// The setup launch of a registration call; boxes: a box per 64 points (the
+// backward pass), else a sphere per tile of the culled forward kernel.
+// Returns the number of status flags it writes.
+gmm_status lik_setup(Run &r, const float *pts, int64_t n, const float *pose6, const float *w,
+                     const float *mu, const float *cov, bool boxes, int *nflags) {
+  const WsLayout &L = r.L;
+  LikSetupArgs a;
+  a.n = n;
+  a.npad = L.npad;
+  a.K = r.K;
+  a.tpts = r.cull ? r.cc.tile : 0;
+  const int blocks = 1 + (int)std::min<int64_t>(kLikMaxBlocks, L.npad / kLikThreads);
+  float4 *bounds = at<float4>(r.ws, L.tsph);
+  hipLaunchKernelGGL(lik_setup_kernel, dim3(blocks), dim3(kLikThreads), 0, r.s, pts, pose6, w,
+                     mu, cov, at<float4>(r.ws, L.pts4), !boxes && r.cull ? bounds : nullptr,
+                     boxes ? bounds : nullptr, at<float>(r.ws, L.cpar[r.cur]),
+                     at<float4>(r.ws, L.shift[r.cur]), at<double>(r.ws, L.th64),
+                     at<double>(r.ws, L.pose64), at<float>(r.ws, L.rt32),
+                     at<uint32_t>(r.ws, L.status), at<uint32_t>(r.ws, L.flags), a);
+  HIP_TRY(hipGetLastError());
+  *nflags = blocks;
   return GMM_OK;
 }
 
@@ -986,13 +1082,13 @@ gmm_status enqueue_fit(Run &r, const float *pts, int64_t n,
                        bool may_tune) {
   gmm_status st;
   if ((st = run_init(r, init_labels != nullptr)) != GMM_OK) return st;
-  if ((st = stage(r, pts, n, init_labels, nullptr, sort_enabled())) != GMM_OK) return st;
+  if ((st = stage(r, pts, n, init_labels, sort_enabled())) != GMM_OK) return st;
   const double reg = opts->reg_covar;
   if (init_labels) {
     // theta_0 = M-step of the one-hot responsibilities, two passes: the mean
     // (shift 0), then the scatter about it.
-    if ((st = run_pass(r, kLabels, kUpdMeanOnly, reg, nullptr, nullptr)) != GMM_OK) return st;
-    if ((st = run_pass(r, kLabels, kUpdFull, reg, nullptr, nullptr)) != GMM_OK) return st;
+    if ((st = run_pass(r, kLabels, kUpdMeanOnly, reg, nullptr)) != GMM_OK) return st;
+    if ((st = run_pass(r, kLabels, kUpdFull, reg, nullptr)) != GMM_OK) return st;
   } else {
     if ((st = run_precompute(r, w, mu, cov)) != GMM_OK) return st;
   }
@@ -1005,14 +1101,14 @@ gmm_status enqueue_fit(Run &r, const float *pts, int64_t n,
   } else for (int t = 0; t < opts->iters; ++t) {
     double *slot = loglik ? loglik + t : nullptr;
     if (opts->moment_mode == GMM_MOMENTS_TWO_PASS) {
-      if ((st = run_pass(r, kSoftStats, kUpdMeanOnly, reg, slot, nullptr)) != GMM_OK) return st;
+      if ((st = run_pass(r, kSoftStats, kUpdMeanOnly, reg, slot)) != GMM_OK) return st;
       slot = nullptr;
     }
-    if ((st = run_pass(r, kSoftStats, kUpdFull, reg, slot, nullptr)) != GMM_OK) return st;
+    if ((st = run_pass(r, kSoftStats, kUpdFull, reg, slot)) != GMM_OK) return st;
   }
   // log-likelihood of the returned parameters and the FP32 outputs
   return run_pass(r, kSoftLogLik, kUpdNone, reg,
-                  loglik ? loglik + opts->iters : nullptr, nullptr, w, mu, cov);
+                  loglik ? loglik + opts->iters : nullptr, w, mu, cov);
 }
 
 // Argument checks, launch configuration and workspace layout of a fit.
@@ -1904,7 +2000,7 @@ size_t gmm_loglik_workspace_size(int64_t n, int32_t k) {
   if (check_sizes(n, k, false) != GMM_OK) return 0;
   TileCfg c;
   if (!pick_cfg(k, n, &c)) return 0;
-  return ws_layout(n, k, c).total;
+  return ws_layout(n, k, c, 0, 0, false, true).total;
 }
 
 gmm_status gmm_loglik(const float *pts, int64_t n, const float *pose6,
@@ -1920,26 +2016,24 @@ gmm_status gmm_loglik(const float *pts, int64_t n, const float *pose6,
   r.K = k;
   if (!pick_cfg(k, n, &r.c)) return fail(GMM_ERR_UNSUPPORTED, "no launch configuration for k=%d", k);
   r.cull = pick_cull_cfg(k, n, &r.cc);
-  r.L = ws_layout(n, k, r.c);
+  r.L = ws_layout(n, k, r.c, 0, 0, false, true);
   r.s = static_cast<hipStream_t>(stream);
   WsGuard guard;
   if ((st = get_ws(&ws, &ws_bytes, r.L.total, r.s, &guard)) != GMM_OK) return st;
   r.ws = ws;
-  if ((st = run_init(r, false)) != GMM_OK) return st;
-  const float *Rt = nullptr;
-  if (pose6) {
-    hipLaunchKernelGGL(pose_kernel, dim3(1), dim3(64), 0, r.s, pose6,
-                       at<double>(ws, r.L.pose64), at<float>(ws, r.L.rt32));
-    HIP_TRY(hipGetLastError());
-    Rt = at<float>(ws, r.L.rt32);
-  }
-  if ((st = stage(r, pts, n, nullptr, Rt)) != GMM_OK) return st;
-  if ((st = run_precompute(r, w, mu, cov)) != GMM_OK) return st;
+  int nflags = 0, rows = 0;
+  if ((st = lik_setup(r, pts, n, pose6, w, mu, cov, false, &nflags)) != GMM_OK) return st;
   if (g_prof.reps > 0) {
     r.sink = &g_prof.pending;
     r.time_loglik = true;
   }
-  return run_pass(r, kSoftLogLik, kUpdNone, 0.0, out_L, out_lse);
+  if ((st = run_tiles(r, kSoftLogLik, kUpdNone, out_lse, nullptr, 0, &rows)) != GMM_OK) return st;
+  hipLaunchKernelGGL(lik_finish_kernel, dim3(1), dim3(kLikFinishThreads), 0, r.s,
+                     at<double>(ws, r.L.part), rows, r.L.ncols, kNStat * k,
+                     at<uint32_t>(ws, r.L.flags), nflags, out_L,
+                     at<uint32_t>(ws, r.L.status));
+  HIP_TRY(hipGetLastError());
+  return GMM_OK;
 }
 
 
@@ -2025,7 +2119,7 @@ gmm_status gmm_fit_batched(int32_t B, const float *pts, const int64_t *pt_off,
       hipLaunchKernelGGL(stage_kernel, dim3((unsigned)((npad + 255) / 256)), dim3(256),
                          0, s, pts + 3 * pt_off[f], n, npad,
                          init_labels ? init_labels + pt_off[f] : nullptr,
-                         bp.base[f].K, nullptr,
+                         bp.base[f].K,
                          at<float4>(ws, stage_to) + bp.base[f].toff * kBatchT,
                          at<uint32_t>(ws, bp.status));
       HIP_TRY(hipGetLastError());
@@ -2263,7 +2357,9 @@ size_t gmm_loglik_backward_workspace_size(int64_t n, int32_t k) {
   TileCfg c;
   BwdCfg bc;
   if (!pick_cfg(k, n, &c) || !pick_bwd_cfg(k, n, &bc)) return 0;
-  return ws_layout(n, k, c, kBwdExtra, bc.grid).total;
+  BwdCullCfg bcc;
+  const int grid = pick_bwd_cull_cfg(k, n, &bcc) ? std::max(bcc.grid, bc.grid) : bc.grid;
+  return ws_layout(n, k, c, kBwdExtra, grid, false, true).total;
 }
 
 gmm_status gmm_loglik_backward(const float *pts, int64_t n, const float *pose6,
@@ -2282,27 +2378,24 @@ gmm_status gmm_loglik_backward(const float *pts, int64_t n, const float *pose6,
   BwdCfg bc;
   if (!pick_cfg(k, n, &r.c) || !pick_bwd_cfg(k, n, &bc))
     return fail(GMM_ERR_UNSUPPORTED, "no backward configuration for k=%d", k);
-  r.L = ws_layout(n, k, r.c, kBwdExtra, bc.grid);
+  // the culled kernel wherever it runs; the dense one for GMM_CULL=0 and
+  // more components than the culled one takes
+  BwdCullCfg bcc;
+  const bool cull = pick_bwd_cull_cfg(k, n, &bcc);
+  r.L = ws_layout(n, k, r.c, kBwdExtra, cull ? std::max(bcc.grid, bc.grid) : bc.grid, false,
+                  true);
   r.s = static_cast<hipStream_t>(stream);
   WsGuard guard;
   if ((st = get_ws(&ws, &ws_bytes, r.L.total, r.s, &guard)) != GMM_OK) return st;
   r.ws = ws;
-  if ((st = run_init(r, false)) != GMM_OK) return st;
-  const float *Rt = nullptr;
-  const double *pose64 = nullptr;
-  if (pose6) {
-    hipLaunchKernelGGL(pose_kernel, dim3(1), dim3(64), 0, r.s, pose6,
-                       at<double>(ws, r.L.pose64), at<float>(ws, r.L.rt32));
-    HIP_TRY(hipGetLastError());
-    Rt = at<float>(ws, r.L.rt32);
-    pose64 = at<double>(ws, r.L.pose64);
-  }
-  if ((st = stage(r, pts, n, nullptr, Rt)) != GMM_OK) return st;
-  if ((st = run_precompute(r, w, mu, cov)) != GMM_OK) return st;
+  int nflags = 0;
+  if ((st = lik_setup(r, pts, n, pose6, w, mu, cov, cull, &nflags)) != GMM_OK) return st;
+  const float *Rt = pose6 ? at<float>(ws, r.L.rt32) : nullptr;
+  const double *pose64 = pose6 ? at<double>(ws, r.L.pose64) : nullptr;
   // the backward kernel has its own tile size (the forward's shape, which a
   // forced or tuned configuration may set to 128 points, does not apply)
   TileArgs a;
-  a.ntiles = (int)(r.L.npad / bc.tile);
+  a.ntiles = (int)(r.L.npad / (cull ? kBwdCullT : bc.tile));
   a.K = k;
   a.KC = k;
   a.P = bc.P;
@@ -2319,25 +2412,29 @@ gmm_status gmm_loglik_backward(const float *pts, int64_t n, const float *pose6,
     g_prof.pending.push_back(pp);
     const int64_t all = (int64_t)g_prof.reps * a.ntiles * k;
     g_prof.pairs_all += all;
-    g_prof.pairs_dense += all;
+    if (cull)
+      a.pairs = g_prof.dpairs;
+    else
+      g_prof.pairs_dense += all;
     HIP_TRY(hipEventRecord(pp.a, r.s));
   }
   for (int rep = 0; rep < (timed ? g_prof.reps : 1); ++rep) {
-    bc.launch(bc, r.s, at<float4>(ws, r.L.pts4), at<float>(ws, r.L.cpar[r.cur]),
-              at<float4>(ws, r.L.shift[r.cur]), Rt, grad_L,
-              at<double>(ws, r.L.part), g_pts, a, n);
+    if (cull)
+      hipLaunchKernelGGL(em_bwd_cull_kernel<kBwdCullRows>, dim3(bcc.grid), dim3(kBwdCullBlock),
+                         bcc.lds, r.s, at<float4>(ws, r.L.pts4), at<float4>(ws, r.L.tsph),
+                         at<float>(ws, r.L.cpar[r.cur]), at<float4>(ws, r.L.shift[r.cur]), Rt,
+                         grad_L, at<double>(ws, r.L.part), g_pts, a, n);
+    else
+      bc.launch(bc, r.s, at<float4>(ws, r.L.pts4), at<float>(ws, r.L.cpar[r.cur]),
+                at<float4>(ws, r.L.shift[r.cur]), Rt, grad_L,
+                at<double>(ws, r.L.part), g_pts, a, n);
     HIP_TRY(hipGetLastError());
   }
   if (timed) HIP_TRY(hipEventRecord(pp.b, r.s));
-  const int ncx = (r.L.ncols + 63) / 64;
-  hipLaunchKernelGGL(reduce_rows_kernel<256>, dim3(ncx, kRedChunks), dim3(256), 0,
-                     r.s, at<double>(ws, r.L.part), bc.grid, r.L.ncols, 0,
-                     at<double>(ws, r.L.red));
-  HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(bwd_finish_kernel, dim3(1), dim3(256), 0, r.s,
-                     at<double>(ws, r.L.red), r.L.ncols, k, w, cov, pose64,
-                     grad_L, g_pose6, g_w, g_mu, g_cov,
-                     at<uint32_t>(ws, r.L.status));
+  hipLaunchKernelGGL(bwd_finish_kernel, dim3(k + 1), dim3(kFuseThreads), 0, r.s,
+                     at<double>(ws, r.L.part), cull ? bcc.grid : bc.grid, r.L.ncols, k,
+                     cull ? 1 : 0, w, cov, pose64, grad_L, at<uint32_t>(ws, r.L.flags), nflags,
+                     g_pose6, g_w, g_mu, g_cov, at<uint32_t>(ws, r.L.status));
   HIP_TRY(hipGetLastError());
   return GMM_OK;
 }
