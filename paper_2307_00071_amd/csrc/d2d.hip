@@ -52,7 +52,7 @@ constexpr int kMaxComp = 65535;   // grid.x = source components
 // Workspace: the state first (its status word at offset 0), then the two
 // mixtures in FP64 and the per-block rows.
 struct D2DLayout {
-  size_t state, src, tgt, rows, total;
+  size_t state, src, tgt, rows, srows, total;
 };
 
 D2DLayout d2d_layout(int m, int n) {
@@ -62,6 +62,8 @@ D2DLayout d2d_layout(int m, int n) {
   L.src = o;   o = align256(o + (size_t)m * 10 * sizeof(double));
   L.tgt = o;   o = align256(o + (size_t)n * 10 * sizeof(double));
   L.rows = o;  o = align256(o + (size_t)m * std::max(2 * kTrials, kNStat) * sizeof(double));
+  // two launches an iteration: the statistics rows beside the value rows
+  L.srows = o; o = align256(o + (m <= kFuseComp ? (size_t)m * kNStat * sizeof(double) : 0));
   L.total = o;
   return L;
 }
@@ -170,7 +172,10 @@ struct Reg {
   }
 };
 
+gmm_status reg_enqueue_fused(const Reg &r, const D2DLayout &L, hipStream_t s);
+
 gmm_status reg_enqueue(const Reg &r, const D2DLayout &L, hipStream_t s) {
+  if (r.m <= kFuseComp) return reg_enqueue_fused(r, L, s);
   void *ws = r.ws;
   const int m = r.m, n = r.n;
   const float *w = r.w, *mu = r.mu, *cov = r.cov, *tw = r.tw, *tmu = r.tmu, *tcov = r.tcov;
@@ -201,6 +206,44 @@ gmm_status reg_enqueue(const Reg &r, const D2DLayout &L, hipStream_t s) {
     }
   }
   hipLaunchKernelGGL(d2d_out_kernel, dim3(1), dim3(64), 0, s, st, T_out, counts);
+  HIP_TRY(hipGetLastError());
+  return GMM_OK;
+}
+
+// The same call, two launches an iteration (m <= kFuseComp).
+gmm_status reg_enqueue_fused(const Reg &r, const D2DLayout &L, hipStream_t s) {
+  State *st = at<State>(r.ws, L.state);
+  const Mix a = mix_of(r.ws, L.src, r.m), b = mix_of(r.ws, L.tgt, r.n);
+  double *vrows = at<double>(r.ws, L.rows), *srows = at<double>(r.ws, L.srows);
+  const int hist_len = r.iters_iso + r.iters_aniso + 2;
+  hipLaunchKernelGGL(d2d_init_kernel, dim3(1), dim3(256), 0, s, st, r.T0, (const double *)nullptr,
+                     r.history, r.history ? hist_len : 0, r.counts);
+  HIP_TRY(hipGetLastError());
+  const int iters[2] = {r.iters_iso, r.iters_aniso};
+  int par = 0, pending = 0;
+  for (int stage = 0; stage < 2; ++stage) {
+    if (iters[stage] == 0) continue;
+    hipLaunchKernelGGL(d2d_it_prep_kernel, dim3((r.m + r.n + kThreads - 1) / kThreads + 1),
+                       dim3(kThreads), 0, s, MixArgs{r.w, r.mu, r.cov}, a,
+                       MixArgs{r.tw, r.tmu, r.tcov}, b, st, stage, par, pending, vrows, r.history,
+                       hist_len);
+    HIP_TRY(hipGetLastError());
+    par = 0;
+    hipLaunchKernelGGL(d2d_it_value_kernel, dim3(r.m), dim3(kThreads), 0, s, a, b, st, vrows);
+    HIP_TRY(hipGetLastError());
+    for (int it = 0; it < iters[stage]; ++it) {
+      hipLaunchKernelGGL(d2d_it_stats_kernel, dim3(r.m), dim3(kThreads), 0, s, a, b, st, par,
+                         it == 0 ? 1 : 0, vrows, srows, r.history, hist_len);
+      HIP_TRY(hipGetLastError());
+      par = 1 - par;
+      hipLaunchKernelGGL(d2d_it_step_kernel, dim3(r.m, kTrials * kThreads / kStepThreads), dim3(kStepThreads), 0, s, a, b, st, par,
+                         srows, vrows);
+      HIP_TRY(hipGetLastError());
+    }
+    pending = 1;
+  }
+  hipLaunchKernelGGL(d2d_it_out_kernel, dim3(1), dim3(kThreads), 0, s, st, par, pending, vrows,
+                     r.m, r.history, hist_len, r.T_out, r.counts);
   HIP_TRY(hipGetLastError());
   return GMM_OK;
 }

@@ -19,7 +19,7 @@
 // is a fixed-order reduction (per thread in j order, a butterfly per wave,
 // waves in order, blocks in order), so results are bitwise reproducible.
 // The optimisation never synchronises with the host: each iteration's
-// kernels read a device "stopped" flag and return at once when the stage has
+// kernels (two, or five for large sources) read a device "stopped" flag and return at once when the stage has
 // ended.
 #pragma once
 
@@ -34,6 +34,7 @@ namespace d2d_dev {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kTrials = 8;          // step sizes 1, 1/2, ..., 2^-7
+constexpr int kFuseComp = 256;      // source components of the two-launch iteration
 constexpr int kPose = 12;           // R row-major (9), t (3)
 constexpr int kNStat = 27;          // H: delta-delta 6, delta-t 9, t-t 6; grad 6
 constexpr double kIsoEps = 1e-3;
@@ -43,6 +44,16 @@ constexpr double kLn2Pi = 1.83787706640934548356;
 constexpr uint32_t kStBadArg = 1u << GMM_ERR_INVALID_ARG;
 constexpr uint32_t kStNotSpd = 1u << GMM_ERR_NOT_SPD;
 constexpr uint32_t kStNonFinite = 1u << GMM_ERR_NONFINITE;
+
+// What an iteration starts from.
+struct Cur {
+  double pose[kPose];
+  double f;
+  int stopped, stage, hist_n;
+  int count[2];
+  int pad;
+};
+static_assert(sizeof(Cur) % sizeof(double) == 0, "copied as doubles");
 
 // Device state; the status word first (gmm_workspace_status reads it).
 struct State {
@@ -56,6 +67,11 @@ struct State {
   double fval[1 + kTrials];          // f at those poses
   double f;                          // f at the current pose
   double grad[6];                    // df/d(delta, dt) at the current pose
+  // the two-launch iteration: the current state, in two copies that take
+  // turns, and the trials of the last step
+  Cur cur[2];
+  int trial_stop;                    // no step: the stage ends
+  double trial[kTrials][kPose];
 };
 
 // A mixture in FP64: ln w, mean, covariance lower triangle (00 10 11 20 21 22).
@@ -149,13 +165,13 @@ __device__ inline void smallest_eigvec(const double *c6, double *v) {
   for (int k = 0; k < 3; ++k) v[k] = V[k][m] / n;
 }
 
-// FP64 copies of one mixture: ln w, mean, covariance (isoplanar when iso).
-__global__ __launch_bounds__(kThreads) void d2d_prep_kernel(
-    const float *__restrict__ w, const float *__restrict__ mu,
-    const float *__restrict__ cov, int n, int iso, double *__restrict__ lw,
-    double *__restrict__ mu64, double *__restrict__ cov64, uint32_t *status) {
-  const int k = blockIdx.x * kThreads + threadIdx.x;
-  if (k >= n) return;
+// FP64 copies of component k of one mixture: ln w, mean, covariance
+// (isoplanar when iso).
+__device__ inline void prep_component(int k, const float *__restrict__ w,
+                                      const float *__restrict__ mu,
+                                      const float *__restrict__ cov, int iso,
+                                      double *__restrict__ lw, double *__restrict__ mu64,
+                                      double *__restrict__ cov64, uint32_t *status) {
   const double wk = w[k];
   if (!(wk > 0.0) || !isfinite(wk)) set_status(status, kStBadArg);
   lw[k] = log(wk);
@@ -177,6 +193,14 @@ __global__ __launch_bounds__(kThreads) void d2d_prep_kernel(
     c6[5] = 1.0 - a * v[2] * v[2];
   }
   for (int j = 0; j < 6; ++j) cov64[6 * k + j] = c6[j];
+}
+
+__global__ __launch_bounds__(kThreads) void d2d_prep_kernel(
+    const float *__restrict__ w, const float *__restrict__ mu,
+    const float *__restrict__ cov, int n, int iso, double *__restrict__ lw,
+    double *__restrict__ mu64, double *__restrict__ cov64, uint32_t *status) {
+  const int k = blockIdx.x * kThreads + threadIdx.x;
+  if (k < n) prep_component(k, w, mu, cov, iso, lw, mu64, cov64, status);
 }
 
 // The state at the start of a call: pose from the 4 x 4 transform or from
@@ -202,7 +226,12 @@ __global__ void d2d_init_kernel(State *st, const double *T0, const double *pose6
     for (int r = 0; r < 3; ++r) p[9 + r] = pose6[3 + r];
   }
   bool fin = true;
-  for (int i = 0; i < kPose; ++i) fin = fin && isfinite(p[i]);
+  for (int i = 0; i < kPose; ++i) {
+    fin = fin && isfinite(p[i]);
+    st->cur[0].pose[i] = p[i];
+  }
+  st->cur[0].hist_n = 0;
+  st->cur[0].count[0] = st->cur[0].count[1] = 0;
   if (!fin) set_status(&st->status, kStNonFinite);
   if (counts) counts[0] = counts[1] = 0;
 }
@@ -270,20 +299,91 @@ __device__ inline bool pair_terms(const SrcTerms &s, double lwi, const double *n
   return true;
 }
 
-// (m, s) pairs: the log-sum-exp m + ln s, merged exactly as written.
+// (m, s) pairs: the log-sum-exp m + ln s; the smaller maximum's sum is
+// scaled.  One exponential and no branch, as the lanes of a wave differ in
+// which side is larger.
 __device__ inline void lse_merge(double &m, double &s, double m2, double s2) {
-  if (s2 == 0.0) return;
-  if (s == 0.0) {
-    m = m2;
-    s = s2;
-    return;
+  const bool up = m2 > m;
+  const double e = exp(up ? m - m2 : m2 - m);
+  const double r = fma(up ? s : s2, e, up ? s2 : s);
+  const bool keep = s2 == 0.0, take = s == 0.0;
+  s = keep ? s : take ? s2 : r;
+  m = keep ? m : take ? m2 : up ? m2 : m;
+}
+
+// The (m, s) pairs of kThreads threads (t of them, its wave and lane from t)
+// merged: a butterfly per wave, then the waves in order; the result in m, s
+// of thread 0.  wm, ws: kWaves doubles of LDS each.  One barrier, which the
+// whole block takes.
+__device__ inline void lse_block(double &m, double &s, double *wm, double *ws, int t) {
+  if (__ballot(s != 0.0) != 0)   // a wave without terms merges nothing
+    for (int off = 32; off > 0; off >>= 1) {
+      const double m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(s, off, 64);
+      lse_merge(m, s, m2, s2);
+    }
+  if ((t & 63) == 0) {
+    wm[t >> 6] = m;
+    ws[t >> 6] = s;
   }
-  if (m2 > m) {
-    s = s * exp(m - m2) + s2;
-    m = m2;
-  } else {
-    s = s + s2 * exp(m2 - m);
+  __syncthreads();
+  if (t == 0)
+    for (int k = 1; k < kWaves; ++k) lse_merge(m, s, wm[k], ws[k]);
+}
+
+// One component in registers (loaded before a launch's other work).
+struct Comp {
+  double lw, mu[3], cov[6];
+};
+__device__ inline Comp load_comp(const Mix &x, int j) {
+  Comp c;
+  c.lw = 0.0;
+  for (int k = 0; k < 3; ++k) c.mu[k] = 0.0;
+  for (int k = 0; k < 6; ++k) c.cov[k] = 0.0;
+  if (j < x.n) {
+    c.lw = x.lw[j];
+    for (int k = 0; k < 3; ++k) c.mu[k] = x.mu[3 * j + k];
+    for (int k = 0; k < 6; ++k) c.cov[k] = x.cov[6 * j + k];
   }
+  return c;
+}
+
+// Source component `a` against every target component at `pose`, by
+// kThreads threads (tj: the target component of thread t): (m, s) into r.
+__device__ inline void value_row(const Comp &a, const Comp &tj, const Mix &tgt,
+                                 const double *pose, int t, double *wm, double *ws, double *r,
+                                 uint32_t *status) {
+  SrcTerms s;
+  if ((t & ~63) < tgt.n) src_terms(pose, a.mu, a.cov, &s);
+  double m = 0.0, sm = 0.0;
+  bool bad = false;
+  for (int j = t; j < tgt.n; j += kThreads) {
+    PairTerms q;
+    const Comp c = j == t ? tj : load_comp(tgt, j);
+    if (!pair_terms(s, a.lw, c.mu, c.cov, c.lw, &q)) {
+      bad = true;
+      continue;
+    }
+    lse_merge(m, sm, q.ell, 1.0);
+  }
+  if (bad) set_status(status, kStNotSpd);
+  lse_block(m, sm, wm, ws, t);
+  if (t == 0) {
+    r[0] = m;
+    r[1] = sm;
+  }
+}
+
+// The log-sum-exp of a pose's M rows, on thread 0: thread t merges rows t,
+// t + 256, ... in order, then waves and the block in order.
+__device__ inline double2 row_of(const double *__restrict__ r, int M, int i) {
+  return i < M ? make_double2(r[2 * i], r[2 * i + 1]) : make_double2(0.0, 0.0);
+}
+__device__ inline double value_of_rows(const double *__restrict__ r, int M, int t, double *wm,
+                                       double *ws, double2 r0) {
+  double m = r0.x, s = r0.y;   // row t
+  for (int i = t + kThreads; i < M; i += kThreads) lse_merge(m, s, r[2 * i], r[2 * i + 1]);
+  lse_block(m, s, wm, ws, t);
+  return (s > 0.0) ? m + log(s) : -INFINITY;
 }
 
 // Value pass: f at pose p0 + blockIdx.y; rows[(p, i)] = (m, s) of source
@@ -292,62 +392,19 @@ __global__ __launch_bounds__(kThreads) void d2d_value_kernel(
     Mix src, Mix tgt, State *st, int p0, double *__restrict__ rows) {
   if (st->stopped) return;
   __shared__ double wm[kWaves], ws[kWaves];
-  const int i = blockIdx.x, p = p0 + blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  SrcTerms s;
-  src_terms(st->pose[p], src.mu + 3 * i, src.cov + 6 * i, &s);
-  const double lwi = src.lw[i];
-  double m = 0.0, sm = 0.0;
-  bool bad = false;
-  for (int j = tid; j < tgt.n; j += kThreads) {
-    PairTerms q;
-    if (!pair_terms(s, lwi, tgt.mu + 3 * j, tgt.cov + 6 * j, tgt.lw[j], &q)) {
-      bad = true;
-      continue;
-    }
-    lse_merge(m, sm, q.ell, 1.0);
-  }
-  if (bad) set_status(&st->status, kStNotSpd);
-  for (int off = 32; off > 0; off >>= 1) {
-    const double m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(sm, off, 64);
-    lse_merge(m, sm, m2, s2);
-  }
-  if (lane == 0) {
-    wm[wv] = m;
-    ws[wv] = sm;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int k = 1; k < kWaves; ++k) lse_merge(m, sm, wm[k], ws[k]);
-    double *r = rows + 2 * ((size_t)blockIdx.y * src.n + i);
-    r[0] = m;
-    r[1] = sm;
-  }
+  value_row(load_comp(src, blockIdx.x), load_comp(tgt, threadIdx.x), tgt,
+            st->pose[p0 + blockIdx.y], threadIdx.x, wm, ws,
+            rows + 2 * ((size_t)blockIdx.y * src.n + blockIdx.x), &st->status);
 }
 
-// fval[p0 + blockIdx.x] = the log-sum-exp of the pose's M rows: thread t
-// merges rows t, t + 256, ... in order, then waves and the block in order.
+// fval[p0 + blockIdx.x] = the log-sum-exp of the pose's M rows.
 __global__ __launch_bounds__(kThreads) void d2d_value_reduce_kernel(
     State *st, int p0, const double *__restrict__ rows, int M) {
   if (st->stopped) return;
   __shared__ double wm[kWaves], ws[kWaves];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const double *r = rows + 2 * (size_t)blockIdx.x * M;
-  double m = 0.0, s = 0.0;
-  for (int i = tid; i < M; i += kThreads) lse_merge(m, s, r[2 * i], r[2 * i + 1]);
-  for (int off = 32; off > 0; off >>= 1) {
-    const double m2 = __shfl_xor(m, off, 64), s2 = __shfl_xor(s, off, 64);
-    lse_merge(m, s, m2, s2);
-  }
-  if (lane == 0) {
-    wm[wv] = m;
-    ws[wv] = s;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int k = 1; k < kWaves; ++k) lse_merge(m, s, wm[k], ws[k]);
-    st->fval[p0 + blockIdx.x] = (s > 0.0) ? m + log(s) : -INFINITY;
-  }
+  const double f = value_of_rows(r, M, threadIdx.x, wm, ws, row_of(r, M, threadIdx.x));
+  if (threadIdx.x == 0) st->fval[p0 + blockIdx.x] = f;
 }
 
 // f at the current pose from fval[0]; appended to the history.
@@ -364,25 +421,23 @@ __global__ void d2d_take_f_kernel(State *st, double *hist, int hist_len) {
 
 // Statistics pass at the current pose: per source component i the 27 sums
 // of gamma_ij (H entries and gradient) into rows[i].
-__global__ __launch_bounds__(kThreads) void d2d_stats_kernel(
-    Mix src, Mix tgt, State *st, double *__restrict__ rows) {
-  if (st->stopped) return;
-  __shared__ double wsum[kWaves][kNStat];
+__device__ inline void stats_row(const Comp &ca, const Comp &tj, const Mix &tgt,
+                                 const double *pose, double f, double *__restrict__ rows) {
+  __shared__ double wsum[kWaves][32];
   const int i = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   SrcTerms s;
-  src_terms(st->pose[0], src.mu + 3 * i, src.cov + 6 * i, &s);
-  const double lwi = src.lw[i];
-  const double f = st->f;
+  src_terms(pose, ca.mu, ca.cov, &s);
   const double *Sp = s.Sp;
   const double SP[9] = {Sp[0], Sp[1], Sp[3], Sp[1], Sp[2], Sp[4], Sp[3], Sp[4], Sp[5]};
   const double *a = s.a;
-  double acc[kNStat];
+  double acc[32];   // kNStat sums, padded for the reduction
 #pragma unroll
-  for (int k = 0; k < kNStat; ++k) acc[k] = 0.0;
+  for (int k = 0; k < 32; ++k) acc[k] = 0.0;
   for (int j = tid; j < tgt.n; j += kThreads) {
     PairTerms q;
-    if (!pair_terms(s, lwi, tgt.mu + 3 * j, tgt.cov + 6 * j, tgt.lw[j], &q)) continue;
+    const Comp cj = j == tid ? tj : load_comp(tgt, j);
+    if (!pair_terms(s, ca.lw, cj.mu, cj.cov, cj.lw, &q)) continue;
     const double gm = exp(q.ell - f);
     const double *L = q.L;
     // g = S^-1 d = L^-T z; P = L^-1; B = S^-1 = P^T P
@@ -440,17 +495,34 @@ __global__ __launch_bounds__(kThreads) void d2d_stats_kernel(
     acc[25] -= gm * g[1];
     acc[26] -= gm * g[2];
   }
+  // the wave's sums as a reduce-scatter: each exchange keeps the half of the
+  // statistics that this side of the pair will own, so lane l ends with
+  // statistic (l >> 1), summed in the order of a butterfly over all of them
+  // (31 exchanges instead of 162)
 #pragma unroll
-  for (int k = 0; k < kNStat; ++k)
-    for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off, 64);
-  if (lane == 0)
-    for (int k = 0; k < kNStat; ++k) wsum[wv][k] = acc[k];
+  for (int off = 32, h = 16; off > 1; off >>= 1, h >>= 1) {
+    const bool hi = (lane & off) != 0;
+#pragma unroll
+    for (int k = 0; k < h; ++k) {
+      const double keep = hi ? acc[k + h] : acc[k];
+      const double send = hi ? acc[k] : acc[k + h];
+      acc[k] = keep + __shfl_xor(send, off, 64);
+    }
+  }
+  acc[0] += __shfl_xor(acc[0], 1, 64);
+  if ((lane & 1) == 0) wsum[wv][lane >> 1] = acc[0];
   __syncthreads();
   if (tid < kNStat) {
     double v = wsum[0][tid];
     for (int k = 1; k < kWaves; ++k) v += wsum[k][tid];
     rows[(size_t)i * kNStat + tid] = v;
   }
+}
+
+__global__ __launch_bounds__(kThreads) void d2d_stats_kernel(
+    Mix src, Mix tgt, State *st, double *__restrict__ rows) {
+  if (st->stopped) return;
+  stats_row(load_comp(src, blockIdx.x), load_comp(tgt, threadIdx.x), tgt, st->pose[0], st->f, rows);
 }
 
 // Sum of the M statistics rows: thread (g, k) adds column k of the rows
@@ -462,17 +534,36 @@ __global__ __launch_bounds__(kThreads) void d2d_stats_kernel(
 constexpr int kStepGroups = 37;
 constexpr int kStepThreads = 1024;   // >= kNStat * kStepGroups
 
-__global__ __launch_bounds__(kStepThreads) void d2d_step_kernel(
-    State *st, const double *__restrict__ rows, int M, const double *pose6,
-    double *out7) {
-  if (st->stopped) return;
-  __shared__ double part[kStepGroups][kNStat];
-  __shared__ double tot[kNStat];
+// tot = the column sums, by kStepThreads threads (two barriers).
+// kHead rows of each group may come preloaded (`head`).
+constexpr int kHead = 7;   // covers M <= kFuseComp
+static_assert(kStepThreads >= kNStat * kStepGroups, "a thread per group and column");
+static_assert(kHead * kStepGroups >= kFuseComp, "every row of a fused call");
+struct RowHead {
+  double u[kHead];
+};
+__device__ inline RowHead stats_head(const double *__restrict__ rows, int M) {
+  const int tid = threadIdx.x, g = tid / kNStat, k = tid - g * kNStat;
+  RowHead h;
+#pragma unroll
+  for (int e = 0; e < kHead; ++e) {
+    const int r = g + e * kStepGroups;
+    h.u[e] = (g < kStepGroups && r < M) ? rows[(size_t)r * kNStat + k] : 0.0;
+  }
+  return h;
+}
+__device__ inline void stats_total(const double *__restrict__ rows, int M,
+                                   double (*part)[kNStat], double *tot,
+                                   const RowHead *head = nullptr) {
   const int tid = threadIdx.x;
   if (tid < kNStat * kStepGroups) {
     const int g = tid / kNStat, k = tid - g * kNStat;
     double v = 0.0;
-    for (int i = g; i < M; i += 16 * kStepGroups) {
+    if (head) {
+#pragma unroll
+      for (int e = 0; e < kHead; ++e) v += head->u[e];
+    }
+    for (int i = head ? M : g; i < M; i += 16 * kStepGroups) {
       double u[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
@@ -491,17 +582,11 @@ __global__ __launch_bounds__(kStepThreads) void d2d_step_kernel(
     tot[tid] = v;
   }
   __syncthreads();
-  if (tid != 0) return;
-  for (int k = 0; k < 6; ++k) st->grad[k] = tot[21 + k];
-  if (out7) {
-    double J[9];
-    left_jacobian(pose6, J);
-    out7[0] = st->f;
-    for (int c = 0; c < 3; ++c)
-      out7[1 + c] = J[c] * tot[21] + J[3 + c] * tot[22] + J[6 + c] * tot[23];
-    for (int c = 0; c < 3; ++c) out7[4 + c] = tot[24 + c];
-    return;
-  }
+}
+
+// x = H^-1 grad; false when H is not positive definite or max |x| <
+// kStepTol.
+__device__ inline bool newton_step(const double *tot, double *x) {
   // full 6 x 6 H from the blocks (delta first, then t)
   double H[6][6];
   const int ij[6][2] = {{0, 0}, {1, 0}, {1, 1}, {2, 0}, {2, 1}, {2, 2}};
@@ -517,10 +602,7 @@ __global__ __launch_bounds__(kStepThreads) void d2d_step_kernel(
   for (int j = 0; j < 6; ++j) {
     double s = H[j][j];
     for (int k = 0; k < j; ++k) s -= L[j][k] * L[j][k];
-    if (!(s > 0.0) || !isfinite(s)) {
-      st->stopped = 1;
-      return;
-    }
+    if (!(s > 0.0) || !isfinite(s)) return false;
     L[j][j] = sqrt(s);
     for (int i2 = j + 1; i2 < 6; ++i2) {
       double t = H[i2][j];
@@ -528,9 +610,9 @@ __global__ __launch_bounds__(kStepThreads) void d2d_step_kernel(
       L[i2][j] = t / L[j][j];
     }
   }
-  double y[6], x[6];
+  double y[6];
   for (int r = 0; r < 6; ++r) {
-    double t = st->grad[r];
+    double t = tot[21 + r];
     for (int k = 0; k < r; ++k) t -= L[r][k] * y[k];
     y[r] = t / L[r][r];
   }
@@ -541,23 +623,53 @@ __global__ __launch_bounds__(kStepThreads) void d2d_step_kernel(
   }
   double xm = 0.0;
   for (int k = 0; k < 6; ++k) xm = fmax(xm, fabs(x[k]));
-  if (!(xm >= kStepTol)) {
-    st->stopped = 1;
+  return xm >= kStepTol;
+}
+
+// Trial k: the pose P moved by 2^-k x.
+__device__ inline void trial_pose(int k, const double *x, const double *P, double *Q) {
+  const double sc = ldexp(1.0, -k);
+  const double wv3[3] = {sc * x[0], sc * x[1], sc * x[2]};
+  double E[9];
+  expso3(wv3, E);
+  for (int r = 0; r < 3; ++r) {
+    for (int c = 0; c < 3; ++c)
+      Q[3 * r + c] = E[3 * r] * P[c] + E[3 * r + 1] * P[3 + c] + E[3 * r + 2] * P[6 + c];
+    Q[9 + r] = P[9 + r] + sc * x[3 + r];
+  }
+}
+
+__global__ __launch_bounds__(kStepThreads) void d2d_step_kernel(
+    State *st, const double *__restrict__ rows, int M, const double *pose6,
+    double *out7) {
+  if (st->stopped) return;
+  __shared__ double part[kStepGroups][kNStat];
+  __shared__ double tot[kNStat];
+  __shared__ double x[6];
+  __shared__ bool go;
+  const int tid = threadIdx.x;
+  stats_total(rows, M, part, tot);
+  if (tid < 6) st->grad[tid] = tot[21 + tid];
+  if (out7) {
+    if (tid != 0) return;
+    double J[9];
+    left_jacobian(pose6, J);
+    out7[0] = st->f;
+    for (int c = 0; c < 3; ++c)
+      out7[1 + c] = J[c] * tot[21] + J[3 + c] * tot[22] + J[6 + c] * tot[23];
+    for (int c = 0; c < 3; ++c) out7[4 + c] = tot[24 + c];
     return;
   }
-  const double *P = st->pose[0];
-  for (int k = 0; k < kTrials; ++k) {
-    const double sc = ldexp(1.0, -k);
-    const double wv3[3] = {sc * x[0], sc * x[1], sc * x[2]};
-    double E[9];
-    expso3(wv3, E);
-    double *Q = st->pose[1 + k];
-    for (int r = 0; r < 3; ++r) {
-      for (int c = 0; c < 3; ++c)
-        Q[3 * r + c] = E[3 * r] * P[c] + E[3 * r + 1] * P[3 + c] + E[3 * r + 2] * P[6 + c];
-      Q[9 + r] = P[9 + r] + sc * x[3 + r];
-    }
+  if (tid == 0) {
+    double xs[6];
+    go = newton_step(tot, xs);
+    if (go)
+      for (int k = 0; k < 6; ++k) x[k] = xs[k];
+    else
+      st->stopped = 1;
   }
+  __syncthreads();
+  if (go && tid < kTrials) trial_pose(tid, x, st->pose[0], st->pose[1 + tid]);
 }
 
 // The first trial that increases f becomes the current pose; none: the
@@ -590,6 +702,184 @@ __global__ void d2d_out_kernel(const State *st, double *T, int *counts) {
   if (counts) {
     counts[0] = st->count[0];
     counts[1] = st->count[1];
+  }
+}
+
+// ------------------------------------------------- two launches an iteration
+//
+// For a source of at most kFuseComp components an iteration is two launches
+// instead of five: every block first forms what it needs of the sums of the
+// launch before (the same bits in every block, block 0 writes them to the
+// state), then does its own source component:
+//   d2d_it_stats_kernel  the accepted trial of the last step, then the 27
+//                        statistics at the new pose;
+//   d2d_it_step_kernel   the step and its trial poses, then the values at
+//                        all eight.
+// What is bound here is launches and short dependent FP64 chains, not
+// arithmetic (10^4 pairs at K = 100).  Five launches took 35.5 us an
+// iteration, and each dependent launch left after a stage has ended about
+// 4 us; two take 17-18 us (step and values 12: sums 3.5, 6 x 6 solve 1.7,
+// trial poses 1, values 3.3; accept and statistics 5.2) and 6.4 us when
+// there is nothing to do: 10 + 30 iterations at K = 100, 885 -> 581 us a
+// call.  The step's blocks come in pairs, four trials each, so that the FP64
+// work spreads over the chip (one block with two rounds of four: 6.5 us a
+// round).  Every block reads the rows of all M source components, M^2 x 43
+// doubles an iteration over the chip, so larger sources keep five launches.
+
+// The state after the last step of an iteration (its kTrials x M rows in
+// vrows), or, for the first one of a stage, f at the stage's pose (M rows).
+// By kThreads threads, the result in *c (LDS); `hist` non-NULL in the one
+// block that keeps the history.
+__device__ inline void accept_step(State *st, int par, bool first,
+                                   const double *__restrict__ vrows, int M, double *hist,
+                                   int hist_len, Cur *c) {
+  __shared__ double wm[kWaves], ws[kWaves];
+  __shared__ double fs;
+  const int tid = threadIdx.x;
+  // everything of the usual case (the first trial) is requested at once
+  double2 r0 = row_of(vrows, M, tid);
+  const double *cp = reinterpret_cast<const double *>(&st->cur[par]);
+  if (tid < (int)(sizeof(Cur) / sizeof(double))) reinterpret_cast<double *>(c)[tid] = cp[tid];
+  const bool ended = !first && st->trial_stop;
+  __syncthreads();
+  if (c->stopped) return;
+  if (ended) {
+    __syncthreads();
+    if (tid == 0) c->stopped = 1;
+    __syncthreads();
+    return;
+  }
+  const double f = c->f;
+  bool took = false;
+  for (int k = 0; k < (first ? 1 : kTrials) && !took; ++k) {
+    if (k > 0) r0 = row_of(vrows + 2 * (size_t)k * M, M, tid);
+    const double v = value_of_rows(vrows + 2 * (size_t)k * M, M, tid, wm, ws, r0);
+    if (tid == 0) fs = v;
+    __syncthreads();
+    took = first || fs > f;
+    if (took && tid == 0) {
+      c->f = fs;
+      if (first) {
+        if (!isfinite(fs)) {
+          set_status(&st->status, kStNonFinite);
+          c->stopped = 1;
+        }
+      } else {
+        for (int e = 0; e < kPose; ++e) c->pose[e] = st->trial[k][e];
+        c->count[c->stage]++;
+      }
+      if (hist && c->hist_n < hist_len) hist[c->hist_n] = fs;
+      c->hist_n++;
+    }
+    __syncthreads();
+  }
+  if (!took && tid == 0) c->stopped = 1;
+  __syncthreads();
+}
+
+struct MixArgs {
+  const float *w, *mu, *cov;
+};
+
+// Both mixtures of a stage; the last block: the state the stage starts from
+// (the pending step of the stage before, when there is one).
+__global__ __launch_bounds__(kThreads) void d2d_it_prep_kernel(
+    MixArgs a, Mix src, MixArgs b, Mix tgt, State *st, int stage, int par, int pending,
+    const double *__restrict__ vrows, double *hist, int hist_len) {
+  if (blockIdx.x + 1 < gridDim.x) {
+    const int k = blockIdx.x * kThreads + threadIdx.x;
+    if (k < src.n)
+      prep_component(k, a.w, a.mu, a.cov, stage == 0, const_cast<double *>(src.lw),
+                     const_cast<double *>(src.mu), const_cast<double *>(src.cov), &st->status);
+    else if (k < src.n + tgt.n)
+      prep_component(k - src.n, b.w, b.mu, b.cov, stage == 0, const_cast<double *>(tgt.lw),
+                     const_cast<double *>(tgt.mu), const_cast<double *>(tgt.cov), &st->status);
+    return;
+  }
+  __shared__ Cur c;
+  if (pending) accept_step(st, par, false, vrows, src.n, hist, hist_len, &c);
+  else if (threadIdx.x == 0) c = st->cur[par];
+  if (threadIdx.x == 0) {
+    c.stopped = 0;
+    c.stage = stage;
+    st->cur[0] = c;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void d2d_it_value_kernel(Mix src, Mix tgt, State *st,
+                                                                double *__restrict__ rows) {
+  __shared__ double wm[kWaves], ws[kWaves];
+  value_row(load_comp(src, blockIdx.x), load_comp(tgt, threadIdx.x), tgt, st->cur[0].pose,
+            threadIdx.x, wm, ws, rows + 2 * blockIdx.x, &st->status);
+}
+
+__global__ __launch_bounds__(kThreads) void d2d_it_stats_kernel(
+    Mix src, Mix tgt, State *st, int par, int first, const double *__restrict__ vrows,
+    double *__restrict__ srows, double *hist, int hist_len) {
+  __shared__ Cur c;
+  const Comp a = load_comp(src, blockIdx.x), tj = load_comp(tgt, threadIdx.x);
+  accept_step(st, par, first != 0, vrows, src.n, blockIdx.x == 0 ? hist : nullptr, hist_len, &c);
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->cur[1 - par] = c;
+  if (c.stopped) return;
+  stats_row(a, tj, tgt, c.pose, c.f, srows);
+}
+
+__global__ __launch_bounds__(kStepThreads) void d2d_it_step_kernel(
+    Mix src, Mix tgt, State *st, int par, const double *__restrict__ srows,
+    double *__restrict__ vrows) {
+  // the rows, the components and the pose are requested before the flag is
+  // looked at: each comes from memory that another XCD has written
+  const int tid = threadIdx.x;
+  const int set = tid / kThreads, t = tid % kThreads;
+  const RowHead head = stats_head(srows, src.n);
+  const Comp a = load_comp(src, blockIdx.x), tj = load_comp(tgt, t);
+  if (st->cur[par].stopped) return;
+  __shared__ double part[kStepGroups][kNStat];
+  __shared__ double tot[kNStat];
+  __shared__ double x[6];
+  __shared__ bool go;
+  __shared__ double trial[kTrials][kPose];
+  constexpr int SETS = kStepThreads / kThreads;   // trials of a block; grid.y = kTrials / SETS
+  __shared__ double wm[SETS][kWaves], ws[SETS][kWaves];
+  stats_total(srows, src.n, part, tot, &head);
+  if (tid == 0) {
+    double xs[6];
+    go = newton_step(tot, xs);
+    if (go)
+      for (int k = 0; k < 6; ++k) x[k] = xs[k];
+    if (blockIdx.x == 0 && blockIdx.y == 0) st->trial_stop = go ? 0 : 1;
+  }
+  __syncthreads();
+  if (!go) return;
+  if (tid < kTrials) {
+    trial_pose(tid, x, st->cur[par].pose, trial[tid]);
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+      for (int e = 0; e < kPose; ++e) st->trial[tid][e] = trial[tid][e];
+  }
+  __syncthreads();
+  const int k = (int)blockIdx.y * SETS + set;
+  value_row(a, tj, tgt, trial[k], t, wm[set], ws[set],
+            vrows + 2 * ((size_t)k * src.n + blockIdx.x), &st->status);
+}
+
+// The pending step, then the current pose as a 4 x 4 transform and the
+// per-stage counts.
+__global__ __launch_bounds__(kThreads) void d2d_it_out_kernel(
+    State *st, int par, int pending, const double *__restrict__ vrows, int M, double *hist,
+    int hist_len, double *T, int *counts) {
+  __shared__ Cur c;
+  if (pending) accept_step(st, par, false, vrows, M, hist, hist_len, &c);
+  else if (threadIdx.x == 0) c = st->cur[par];
+  if (threadIdx.x != 0) return;
+  for (int r = 0; r < 3; ++r) {
+    for (int j = 0; j < 3; ++j) T[4 * r + j] = c.pose[3 * r + j];
+    T[4 * r + 3] = c.pose[9 + r];
+  }
+  T[12] = T[13] = T[14] = 0.0;
+  T[15] = 1.0;
+  if (counts) {
+    counts[0] = c.count[0];
+    counts[1] = c.count[1];
   }
 }
 
