@@ -357,6 +357,79 @@ __device__ __forceinline__ void em_update_block(const double *tot, int K, int um
   }
 }
 
+// The mean of one component from its sums tot[j * st] (N0, S1, ...) about
+// the shift; false when they are not finite.
+__device__ __forceinline__ bool component_mean(const double *tot, int st, float4 mf, double *mu) {
+  const double N0 = tot[0];
+  const double S1[3] = {tot[st], tot[2 * st], tot[3 * st]};
+  const double m[3] = {mf.x, mf.y, mf.z};
+  const double rN = 1.0 / (N0 + kEpsN);
+  for (int j = 0; j < 3; ++j) mu[j] = (S1[j] + N0 * m[j]) * rN;
+  return isfinite(N0) && isfinite(S1[0]) && isfinite(S1[1]) && isfinite(S1[2]);
+}
+
+// The M-step of one component with the static bound (lambda > 0), which
+// needs no other component: its sums tot[j * st], j < kNStat, about the shift
+// mf; lnZ and Ntot as in FuseArgs.
+__device__ __forceinline__ void update_component_static(const double *tot, int st, float4 mf,
+                                                        double reg, double lnZ, double Ntot,
+                                                        float *qq, float4 *shift_out, double *t,
+                                                        uint32_t *status) {
+  const double N0 = tot[0];
+  const double S1[3] = {tot[st], tot[2 * st], tot[3 * st]};
+  const double m[3] = {mf.x, mf.y, mf.z};
+  const double Nb = N0 + kEpsN;
+  const double rN = 1.0 / Nb;
+  double mu[3], dl[3];
+  for (int j = 0; j < 3; ++j) {
+    mu[j] = (S1[j] + N0 * m[j]) * rN;
+    dl[j] = mu[j] - m[j];
+  }
+  bool fin = isfinite(N0) && isfinite(S1[0]) && isfinite(S1[1]) && isfinite(S1[2]);
+  const int ij[6][2] = {{0, 0}, {1, 0}, {1, 1}, {2, 0}, {2, 1}, {2, 2}};
+  double C[6];
+  for (int j = 0; j < 6; ++j) {
+    const int r = ij[j][0], c = ij[j][1];
+    const double s2 = tot[(4 + j) * st];
+    const double v = s2 - S1[r] * dl[c] - dl[r] * S1[c] + N0 * dl[r] * dl[c];
+    C[j] = v * rN + ((r == c) ? reg : 0.0);
+    fin = fin && isfinite(s2);
+  }
+  if (!fin) set_status(status, kStNonFinite);
+  double P[6];
+  double cb = -INFINITY;
+  if (chol_inv3(C, P)) cb = log(Nb * P[0] * P[2] * P[5]);
+  if (!isfinite(cb)) set_status(status, kStNotSpd);
+  t[0] = Nb / Ntot;
+  for (int j = 0; j < 3; ++j) t[1 + j] = mu[j];
+  for (int j = 0; j < 6; ++j) t[4 + j] = C[j];
+  t[10] = Nb;
+  *shift_out = make_float4((float)mu[0], (float)mu[1], (float)mu[2], 0.0f);
+  if (isfinite(cb)) {
+    store_eblock(qq, mu, P);
+    qq[3] = (float)((cb - lnZ) * kLog2e);
+  } else {
+    qq[0] = (float)mu[0]; qq[1] = (float)mu[1]; qq[2] = (float)mu[2];
+    for (int j = 0; j < 6; ++j) qq[4 + j] = 0.0f;
+    qq[10] = 0.0f;
+    qq[3] = -INFINITY;
+  }
+}
+
+// One component of the FP64 state as the caller's float32 outputs.
+__device__ __forceinline__ void write_component(const double *t, int b, float *out_w,
+                                                float *out_mu, float *out_cov) {
+  out_w[b] = (float)t[0];
+  for (int j = 0; j < 3; ++j) out_mu[3 * b + j] = (float)t[1 + j];
+  float *cv = out_cov + 9 * b;
+  cv[0] = (float)t[4];
+  cv[1] = cv[3] = (float)t[5];
+  cv[4] = (float)t[6];
+  cv[2] = cv[6] = (float)t[7];
+  cv[5] = cv[7] = (float)t[8];
+  cv[8] = (float)t[9];
+}
+
 // Caller-supplied theta_0 (FP32 w, mu, cov) -> FP64 state and E-step block;
 // weights used as given.  One block of kPreThreads threads.
 constexpr int kPreThreads = 1024;
@@ -460,16 +533,19 @@ __device__ inline void pose_terms(const float *__restrict__ pose6, double *pose6
   }
 }
 
-// Clears the status word and the ticket counters and, for a label start,
-// the shift array (the first label pass accumulates about the origin).
+// Clears the status word and the counters; for a label start the shift array
+// (the first label pass accumulates about the origin); for a one-launch fit
+// its exchange words.
 __global__ void init_kernel(uint32_t *status, unsigned *counters, int ncnt,
-                            float4 *shift, int K) {
+                            float4 *shift, int K, uint64_t *words = nullptr,
+                            int64_t nwords = 0) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int stride = gridDim.x * blockDim.x;
   if (i == 0) *status = 0u;
   for (int j = i; j < ncnt; j += stride) counters[j] = 0u;
   if (shift)
     for (int b = i; b < K; b += stride) shift[b] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int64_t j = i; j < nwords; j += stride) words[j] = 0;
 }
 
 // ------------------------------------------------------------ tile kernel
@@ -1723,16 +1799,7 @@ __device__ __forceinline__ void update_body(const UpdPtrs &q, const UpdArgs &a,
     }
   } else if (q.out_w) {
     for (int b = tid; b < K; b += kUpdThreads) {
-      const double *t = q.th64 + (size_t)b * kTh64Stride;
-      q.out_w[b] = (float)t[0];
-      for (int j = 0; j < 3; ++j) q.out_mu[3 * b + j] = (float)t[1 + j];
-      float *cv = q.out_cov + 9 * b;
-      cv[0] = (float)t[4];
-      cv[1] = cv[3] = (float)t[5];
-      cv[4] = (float)t[6];
-      cv[2] = cv[6] = (float)t[7];
-      cv[5] = cv[7] = (float)t[8];
-      cv[8] = (float)t[9];
+      write_component(q.th64 + (size_t)b * kTh64Stride, b, q.out_w, q.out_mu, q.out_cov);
     }
   }
 }
@@ -1833,33 +1900,14 @@ __global__ __launch_bounds__(kFuseThreads) void reduce_update_kernel(
   if (tid != 0) return;
   if (a.umode == kUpdNone) {
     if (q.out_w) {
-      const double *t = q.th64 + (size_t)b * kTh64Stride;
-      q.out_w[b] = (float)t[0];
-      for (int j = 0; j < 3; ++j) q.out_mu[3 * b + j] = (float)t[1 + j];
-      float *cv = q.out_cov + 9 * b;
-      cv[0] = (float)t[4];
-      cv[1] = cv[3] = (float)t[5];
-      cv[4] = (float)t[6];
-      cv[2] = cv[6] = (float)t[7];
-      cv[5] = cv[7] = (float)t[8];
-      cv[8] = (float)t[9];
+      write_component(q.th64 + (size_t)b * kTh64Stride, b, q.out_w, q.out_mu, q.out_cov);
     }
     return;
   }
-  const double N0 = tot[0];
-  const double S1[3] = {tot[1], tot[2], tot[3]};
-  const float4 mf = q.shift_in[b];
-  const double m[3] = {mf.x, mf.y, mf.z};
-  const double Nb = N0 + kEpsN;
-  const double rN = 1.0 / Nb;
-  double mu[3], dl[3];
-  for (int j = 0; j < 3; ++j) {
-    mu[j] = (S1[j] + N0 * m[j]) * rN;
-    dl[j] = mu[j] - m[j];
-  }
-  bool fin = isfinite(N0) && isfinite(S1[0]) && isfinite(S1[1]) && isfinite(S1[2]);
   if (a.umode == kUpdMeanOnly) {
-    if (!fin) set_status(q.status, kStNonFinite);
+    const float4 mf = q.shift_in[b];
+    double mu[3];
+    if (!component_mean(tot, 1, mf, mu)) set_status(q.status, kStNonFinite);
     q.shift_out[b] = make_float4((float)mu[0], (float)mu[1], (float)mu[2], 0.0f);
     for (int j = 0; j < kParStride; ++j)
       q.cpar_out[(size_t)b * kParStride + j] = q.cpar_in[(size_t)b * kParStride + j];
@@ -1868,36 +1916,9 @@ __global__ __launch_bounds__(kFuseThreads) void reduce_update_kernel(
           *reinterpret_cast<const double *>(q.cpar_in + (size_t)K * kParStride);
     return;
   }
-  const int ij[6][2] = {{0, 0}, {1, 0}, {1, 1}, {2, 0}, {2, 1}, {2, 2}};
-  double C[6];
-  for (int j = 0; j < 6; ++j) {
-    const int r = ij[j][0], c = ij[j][1];
-    const double s2 = tot[4 + j];
-    const double v = s2 - S1[r] * dl[c] - dl[r] * S1[c] + N0 * dl[r] * dl[c];
-    C[j] = v * rN + ((r == c) ? a.reg : 0.0);
-    fin = fin && isfinite(s2);
-  }
-  if (!fin) set_status(q.status, kStNonFinite);
-  double P[6];
-  double cb = -INFINITY;
-  if (chol_inv3(C, P)) cb = log(Nb * P[0] * P[2] * P[5]);
-  if (!isfinite(cb)) set_status(q.status, kStNotSpd);
-  double *t = q.th64 + (size_t)b * kTh64Stride;
-  t[0] = Nb / a.Ntot;
-  for (int j = 0; j < 3; ++j) t[1 + j] = mu[j];
-  for (int j = 0; j < 6; ++j) t[4 + j] = C[j];
-  t[10] = Nb;
-  q.shift_out[b] = make_float4((float)mu[0], (float)mu[1], (float)mu[2], 0.0f);
-  float *qq = q.cpar_out + (size_t)b * kParStride;
-  if (isfinite(cb)) {
-    store_eblock(qq, mu, P);
-    qq[3] = (float)((cb - a.lnZ) * kLog2e);
-  } else {
-    qq[0] = (float)mu[0]; qq[1] = (float)mu[1]; qq[2] = (float)mu[2];
-    for (int j = 0; j < 6; ++j) qq[4 + j] = 0.0f;
-    qq[10] = 0.0f;
-    qq[3] = -INFINITY;
-  }
+  update_component_static(tot, 1, q.shift_in[b], a.reg, a.lnZ, a.Ntot,
+                          q.cpar_out + (size_t)b * kParStride, q.shift_out + b,
+                          q.th64 + (size_t)b * kTh64Stride, q.status);
   if (b == 0) {
     *reinterpret_cast<double *>(q.cpar_out + (size_t)K * kParStride) = a.Chdr;
     // stopping rule (block 0 holds the log-likelihood column)
@@ -2165,17 +2186,7 @@ __global__ __launch_bounds__(kUpdThreads) void update_frames_kernel(
                                  shift_out + F.koff, t64, scratch, status);
   } else if (out_w) {
     for (int b = tid; b < K; b += kUpdThreads) {
-      const double *t = t64 + (size_t)b * kTh64Stride;
-      const int gb = F.koff + b;
-      out_w[gb] = (float)t[0];
-      for (int j = 0; j < 3; ++j) out_mu[3 * gb + j] = (float)t[1 + j];
-      float *cv = out_cov + 9 * gb;
-      cv[0] = (float)t[4];
-      cv[1] = cv[3] = (float)t[5];
-      cv[4] = (float)t[6];
-      cv[2] = cv[6] = (float)t[7];
-      cv[5] = cv[7] = (float)t[8];
-      cv[8] = (float)t[9];
+      write_component(t64 + (size_t)b * kTh64Stride, F.koff + b, out_w, out_mu, out_cov);
     }
   }
 }

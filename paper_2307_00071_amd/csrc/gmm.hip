@@ -601,6 +601,8 @@ struct WsLayout {
   size_t raw4 = 0, keys[2] = {0, 0}, vals[2] = {0, 0}, hist = 0, dtot = 0, box6 = 0;
   int sort_blocks = 0;
   size_t flags = 0;   // registration calls: a status word per setup block
+  size_t words = 0;   // one-launch fits: the exchange words (nwords 64-bit)
+  int64_t nwords = 0;
   int64_t npad;
   int ncols, nslots;
 };
@@ -616,8 +618,7 @@ WsLayout ws_layout(int64_t n, int K, const TileCfg &c, int extra_cols = 0,
   L.nslots = std::max(std::max(c.grid, grid_override), max_grid(K, n));
   L.npad = ((n + 255) / 256) * 256;   // a multiple of every tile size
   L.status = o; o = align256(o + 256);
-  // stopping rule state (words 0-3), the one-launch fit's grid barrier
-  // ticket and give-up flag (words 4, 5)
+  // stopping rule state (words 0-3), the one-launch fit's give-up flag (5)
   L.counter = o; o = align256(o + 8 * sizeof(unsigned));
   L.pose64 = o; o = align256(o + 32 * sizeof(double));
   L.rt32 = o; o = align256(o + 16 * sizeof(float));
@@ -633,6 +634,10 @@ WsLayout ws_layout(int64_t n, int K, const TileCfg &c, int extra_cols = 0,
   L.tsph = o; o = align256(o + (size_t)(L.npad / 64) * (lik ? 2 : 1) * sizeof(float4));
   if (lik) {
     L.flags = o; o = align256(o + (size_t)(kLikMaxBlocks + 1) * sizeof(uint32_t));
+  }
+  if (with_sort && K <= kSmallMaxK && L.npad / kSmallThreads <= kSmallMaxTiles) {
+    L.nwords = small_words(L.npad / kSmallThreads, L.ncols);
+    L.words = o; o = align256(o + (size_t)L.nwords * sizeof(uint64_t));
   }
   if (with_sort && L.npad <= kSortMaxN) {
     L.sort_blocks = (int)((L.npad + kSortChunk - 1) / kSortChunk);
@@ -818,6 +823,16 @@ gmm_status run_tiles(Run &r, int mode, int umode, float *lse, const unsigned *co
   return GMM_OK;
 }
 
+// The static bound C = -3/2 ln(lambda) - 3/2 ln(2 pi) - ln K: every c_b is at
+// most C + ln K (the largest term of a point's sum at most K in value, the
+// sum at most K^2: no FP32 overflow), and a typical weight 1/K puts c_b - C
+// near 0, where its float32 rounding is smallest.
+void static_bound(const Run &r, double reg, double *Ntot, double *lnZ, double *Chdr) {
+  *Ntot = (double)r.n + r.K * kEpsN;
+  *lnZ = log(*Ntot) - 1.5 * log(reg) - log((double)r.K);
+  *Chdr = (-1.5 * log(reg) - 1.5 * kLn2Pi - log((double)r.K)) * kLog2e;
+}
+
 // One pass: the tile kernel, then the reduction and the M-step update.
 gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot,
                     float *out_w = nullptr, float *out_mu = nullptr,
@@ -860,13 +875,7 @@ gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot
     fa.mode = mode;
     fa.umode = umode;
     fa.reg = reg;
-    // the bound C = -3/2 ln(lambda) - 3/2 ln(2 pi) - ln K: every c_b is at
-    // most C + ln K (the largest term of a point's sum at most K in value,
-    // the sum at most K^2: no FP32 overflow), and a typical weight 1/K puts
-    // c_b - C near 0, where its float32 rounding is smallest
-    fa.Ntot = (double)r.n + r.K * kEpsN;
-    fa.lnZ = log(fa.Ntot) - 1.5 * log(reg) - log((double)r.K);
-    fa.Chdr = (-1.5 * log(reg) - 1.5 * kLn2Pi - log((double)r.K)) * kLog2e;
+    static_bound(r, reg, &fa.Ntot, &fa.lnZ, &fa.Chdr);
     fa.tol_abs = r.tol_abs;
     hipLaunchKernelGGL(reduce_update_kernel, dim3(r.K), dim3(kFuseThreads), 0, r.s,
                        at<double>(r.ws, L.part), q, fa);
@@ -911,11 +920,13 @@ gmm_status run_pass(Run &r, int mode, int umode, double reg, double *loglik_slot
 }
 
 gmm_status run_init(Run &r, bool zero_shift) {
-  hipLaunchKernelGGL(init_kernel, dim3(1), dim3(256), 0, r.s,
+  const int64_t nwords = r.small ? r.L.nwords : 0;
+  const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(256, nwords / 1024));
+  hipLaunchKernelGGL(init_kernel, dim3(blocks), dim3(256), 0, r.s,
                      at<uint32_t>(r.ws, r.L.status),
                      at<unsigned>(r.ws, r.L.counter), 8,
                      zero_shift ? at<float4>(r.ws, r.L.shift[r.cur]) : nullptr,
-                     r.K);
+                     r.K, nwords ? at<uint64_t>(r.ws, r.L.words) : nullptr, nwords);
   HIP_TRY(hipGetLastError());
   return GMM_OK;
 }
@@ -1027,29 +1038,28 @@ gmm_status finish(Run &r, bool sync, bool may_alloc = true) {
 }
 
 // Fits with K <= 16 components and at most 256 tiles of 256 points (and
-// no more tiles than compute units) with shifted moments run their soft
-// iterations in one launch of em_small_fit_kernel: one block per tile, all
-// resident at once.  GMM_SMALL=0, or a tile shape forced by GMM_TILE_SHAPE,
-// keeps a launch pair per iteration.
+// no more tiles than compute units) with shifted moments run in one launch
+// of em_small_fit_kernel: one block per tile, all resident at once.
+// GMM_SMALL=0, or a tile shape forced by GMM_TILE_SHAPE, keeps a launch pair
+// per pass.
 int small_give_up() {
   const char *e = getenv("GMM_SMALL_TEST_GIVE_UP");
   return e ? atoi(e) : -1;
 }
 
-bool small_fit_ok(int K, const WsLayout &L, const gmm_fit_opts *opts) {
+bool small_fit_ok(const WsLayout &L, const gmm_fit_opts *opts) {
   const char *e = getenv("GMM_SMALL");
   if ((e && e[0] == '0') || getenv("GMM_TILE_SHAPE")) return false;
-  const int64_t nt = L.npad / kSmallThreads;
-  return K <= kSmallMaxK && nt <= kSmallMaxTiles && nt <= dev_info().cus &&
-         2 * nt <= L.nslots && opts->moment_mode == GMM_MOMENTS_SHIFTED &&
-         opts->iters > 0;
+  return L.nwords > 0 && L.npad / kSmallThreads <= dev_info().cus &&
+         opts->moment_mode == GMM_MOMENTS_SHIFTED && opts->iters > 0;
 }
 
-// The soft iterations of a small fit: parameters cur -> 1 - cur, the
-// log-likelihood of iteration t into loglik[t].
-gmm_status run_small(Run &r, int iters, double reg, double *loglik) {
+// A whole small fit from the labels, or from parameters in set `cur`.
+gmm_status run_small(Run &r, const float *pts, int64_t n, const int32_t *labels, int iters,
+                     double reg, double *loglik, float *w, float *mu, float *cov) {
   const WsLayout &L = r.L;
   SmallArgs a;
+  a.n = n;
   a.K = r.K;
   int P = 1;   // point subsets: the largest power of two with P K <= 256
   while (2 * P * r.K <= kSmallThreads) P *= 2;
@@ -1059,19 +1069,21 @@ gmm_status run_small(Run &r, int iters, double reg, double *loglik) {
   a.ncols = L.ncols;
   a.reg = reg;
   a.tol_abs = r.tol_abs;
-  // GMM_SMALL_TEST_GIVE_UP=t: block 0 gives up at the barrier of iteration t
+  // the dense tile kernel's float32 groups, where they divide a subset
+  a.lab_trip = !labels ? 0 : a.trip % r.c.trip == 0 ? r.c.trip : 1;
+  a.fused = r.fused ? 1 : 0;
+  a.lnZ = a.Ntot = a.Chdr = 0.0;
+  if (r.fused) static_bound(r, reg, &a.Ntot, &a.lnZ, &a.Chdr);
+  // GMM_SMALL_TEST_GIVE_UP=t: block 0 gives up at the exchange of iteration t
   // (tests of the error path; every block still exits)
   a.give_up_at = small_give_up();
   const int grid = (int)(L.npad / kSmallThreads);
-  const int nxt = 1 - r.cur;
-  hipLaunchKernelGGL(em_small_fit_kernel, dim3(grid), dim3(kSmallThreads), 0, r.s,
-                     at<float4>(r.ws, L.pts4), at<float>(r.ws, L.cpar[r.cur]),
-                     at<float4>(r.ws, L.shift[r.cur]), at<float>(r.ws, L.cpar[nxt]),
-                     at<float4>(r.ws, L.shift[nxt]), at<double>(r.ws, L.th64),
-                     at<double>(r.ws, L.part), at<unsigned>(r.ws, L.counter) + 4,
-                     loglik, at<uint32_t>(r.ws, L.status), a);
+  a.two_hops = grid * L.ncols > kSmallOneHop ? 1 : 0;
+  hipLaunchKernelGGL(em_small_fit_kernel, dim3(grid), dim3(kSmallThreads), 0, r.s, pts, labels,
+                     at<float>(r.ws, L.cpar[r.cur]), at<float4>(r.ws, L.shift[r.cur]),
+                     at<uint64_t>(r.ws, L.words), at<unsigned>(r.ws, L.counter) + 5, loglik, w,
+                     mu, cov, at<uint32_t>(r.ws, L.status), a);
   HIP_TRY(hipGetLastError());
-  r.cur = nxt;
   return GMM_OK;
 }
 
@@ -1082,6 +1094,10 @@ gmm_status enqueue_fit(Run &r, const float *pts, int64_t n,
                        bool may_tune) {
   gmm_status st;
   if ((st = run_init(r, init_labels != nullptr)) != GMM_OK) return st;
+  if (r.small) {
+    if (!init_labels && (st = run_precompute(r, w, mu, cov)) != GMM_OK) return st;
+    return run_small(r, pts, n, init_labels, opts->iters, opts->reg_covar, loglik, w, mu, cov);
+  }
   if ((st = stage(r, pts, n, init_labels, sort_enabled())) != GMM_OK) return st;
   const double reg = opts->reg_covar;
   if (init_labels) {
@@ -1092,13 +1108,11 @@ gmm_status enqueue_fit(Run &r, const float *pts, int64_t n,
   } else {
     if ((st = run_precompute(r, w, mu, cov)) != GMM_OK) return st;
   }
-  if (may_tune && !r.cull && !r.small && autotune_on() && forced_candidate() < 0 &&
+  if (may_tune && !r.cull && autotune_on() && forced_candidate() < 0 &&
       tuned_candidate(r.K, n) < 0 &&
       (st = autotune(r, n)) != GMM_OK)
     return st;
-  if (r.small) {
-    if ((st = run_small(r, opts->iters, reg, loglik)) != GMM_OK) return st;
-  } else for (int t = 0; t < opts->iters; ++t) {
+  for (int t = 0; t < opts->iters; ++t) {
     double *slot = loglik ? loglik + t : nullptr;
     if (opts->moment_mode == GMM_MOMENTS_TWO_PASS) {
       if ((st = run_pass(r, kSoftStats, kUpdMeanOnly, reg, slot)) != GMM_OK) return st;
@@ -1141,10 +1155,9 @@ gmm_status fit_setup(const float *pts, int64_t n, int32_t k, const float *w,
   r->cull = pick_cull_cfg(k, n, &r->cc);
   if (r->cull) debug_cfg("fit", k, n, r->cc.name, r->cc.grid, r->cc.block, r->cc.lds);
   r->L = ws_layout(n, k, r->c, 0, 0, true);
-  // a one-launch fit runs its label and final passes dense: the spatial
-  // order and the tile spheres of culling would cost more than they save.
+  // a one-launch fit needs neither the spatial order nor the tile spheres.
   // Profiled fits (per-pass tile timing) keep the launch pairs.
-  r->small = g_prof.reps == 0 && small_fit_ok(k, r->L, opts);
+  r->small = g_prof.reps == 0 && small_fit_ok(r->L, opts);
   if (r->small) r->cull = false;
   r->s = static_cast<hipStream_t>(stream);
   return GMM_OK;
