@@ -2212,26 +2212,84 @@ gmm_status gmm_fit_batched(int32_t B, const float *pts, const int64_t *pt_off,
 // ------------------------------------------------------- k-means++ seeding
 
 struct KppLayout {
-  size_t status, D, T, D2, T2, total;
+  size_t status, D[2], T[2], side[2], dmax, box, total;
   int64_t nch;
-  bool fused;   // one launch per round (double-buffered D, T)
+  bool rounds, cull;   // one launch per round; its culled form
 };
 
 KppLayout kpp_layout(int64_t n) {
-  KppLayout L;
+  KppLayout L = {};
   L.nch = (n + kKppChunk - 1) / kKppChunk;
+  L.rounds = L.nch <= kKppRoundChunks;
+  L.cull = L.rounds && L.nch > kKppSmallChunks;
   size_t o = 0;
   L.status = o; o = align256(o + sizeof(uint32_t));
-  L.D = o; o = align256(o + (size_t)n * sizeof(double));
-  L.T = o; o = align256(o + (size_t)L.nch * sizeof(double));
-  L.fused = L.nch <= kKppFuseChunks;
-  L.D2 = L.T2 = 0;
-  if (L.fused) {
-    L.D2 = o; o = align256(o + (size_t)n * sizeof(double));
-    L.T2 = o; o = align256(o + (size_t)L.nch * sizeof(double));
+  for (int i = 0; i < (L.rounds ? 2 : 1); ++i) {
+    L.D[i] = o; o = align256(o + (size_t)n * sizeof(double));
+    L.T[i] = o; o = align256(o + (size_t)(L.nch + kKppSelPer) * sizeof(double));
+  }
+  if (L.cull) {
+    for (int i = 0; i < 2; ++i) {
+      L.side[i] = o; o = align256(o + (size_t)L.nch);   // read in 16-byte words
+    }
+    L.dmax = o; o = align256(o + (size_t)L.nch * sizeof(double));
+    L.box = o; o = align256(o + (size_t)L.nch * 6 * sizeof(float));
   }
   L.total = o;
   return L;
+}
+
+// The rounds of a seeding, one launch each.
+gmm_status kpp_rounds(const KppLayout &L, const float *pts, int64_t n, int32_t k,
+                      const double *u, int64_t *centres, int32_t *labels, void *ws,
+                      hipStream_t s) {
+  KppState st = {};
+  for (int i = 0; i < 2; ++i) {
+    st.D[i] = at<double>(ws, L.D[i]);
+    st.T[i] = at<double>(ws, L.T[i]);
+  }
+  if (L.cull) {
+    for (int i = 0; i < 2; ++i) st.side[i] = at<uint8_t>(ws, L.side[i]);
+    st.dmax = at<double>(ws, L.dmax);
+    st.box = at<float>(ws, L.box);
+  }
+  uint32_t *status = at<uint32_t>(ws, L.status);
+  hipLaunchKernelGGL(kpp_round0_kernel, dim3((unsigned)L.nch), dim3(kKppChunk), 0, s, pts, n,
+                     centres, st, labels, status);
+  HIP_TRY(hipGetLastError());
+  const int cus = std::max(1, dev_info().cus);
+  const int per =
+      L.cull ? (int)std::min<int64_t>((L.nch + cus - 1) / cus, kKppMaxPer) : kKppUpdChunks;
+  const dim3 grid((unsigned)((L.nch + per - 1) / per));
+  const size_t lds = (size_t)per * kKppRow * sizeof(double);
+  // the fewest threads whose stage covers the totals
+  const bool half = L.nch <= (int64_t)(kKppSelThreads / 2) * kKppSelPer;
+  const auto cull = half ? &kpp_round_cull_kernel<kKppSelThreads / 2>
+                         : &kpp_round_cull_kernel<kKppSelThreads>;
+  const dim3 threads(half ? kKppSelThreads / 2 : kKppSelThreads);
+  if (L.cull && lds > 65536 &&
+      hipFuncSetAttribute(reinterpret_cast<const void *>(cull),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return fail(GMM_ERR_DEVICE, "LDS of the seeding round");
+  // the last centre changes labels alone: without labels it is only picked
+  const int rounds = labels ? k : k - 1;
+  for (int j = 1; j < rounds; ++j) {
+    if (L.cull)
+      hipLaunchKernelGGL(cull, grid, threads, lds, s, pts, n, L.nch, per, u, j, centres, st,
+                         labels);
+    else
+      hipLaunchKernelGGL(kpp_round_kernel, grid, dim3(kKppUpdThreads), 0, s, pts, n, u, j,
+                         centres, st.D[(j - 1) & 1], st.T[(j - 1) & 1], st.D[j & 1], st.T[j & 1],
+                         L.nch, labels);
+    HIP_TRY(hipGetLastError());
+  }
+  if (!labels && k >= 2) {
+    hipLaunchKernelGGL(kpp_last_kernel, dim3(1), dim3(kKppSelThreads), 0, s, pts, n, u, k - 1,
+                       centres, st.D[L.cull ? 0 : k & 1], st.D[1],
+                       L.cull ? st.side[k & 1] : nullptr, st.T[k & 1]);
+    HIP_TRY(hipGetLastError());
+  }
+  return GMM_OK;
 }
 
 size_t gmm_kmeanspp_workspace_size(int64_t n, int32_t k) {
@@ -2252,49 +2310,37 @@ gmm_status gmm_kmeanspp(const float *pts, int64_t n, int32_t k, const double *u,
   WsGuard guard;
   if ((st = get_ws(&ws, &ws_bytes, L.total, s, &guard)) != GMM_OK) return st;
   uint32_t *status = at<uint32_t>(ws, L.status);
-  double *D = at<double>(ws, L.D), *T = at<double>(ws, L.T);
   hipLaunchKernelGGL(init_kernel, dim3(1), dim3(256), 0, s, status, nullptr, 0,
                      nullptr, 0);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(kpp_first_kernel, dim3(1), dim3(256), 0, s, u, k, n, centres,
                      status);
   HIP_TRY(hipGetLastError());
-  const dim3 ugrid((unsigned)((L.nch + kKppUpdChunks - 1) / kKppUpdChunks));
-  if (L.fused && k >= 2) {
-    // round j: centre j from buffer (j - 1) & 1, distances into buffer j & 1
-    double *Db[2] = {D, at<double>(ws, L.D2)}, *Tb[2] = {T, at<double>(ws, L.T2)};
-    hipLaunchKernelGGL(kpp_update_kernel, ugrid, dim3(kKppUpdThreads), 0, s, pts, n, centres, 0,
-                       Db[0], Tb[0], L.nch, status);
-    HIP_TRY(hipGetLastError());
-    for (int j = 1; j + 1 < k; ++j) {
-      hipLaunchKernelGGL(kpp_round_kernel, ugrid, dim3(kKppUpdThreads), 0, s, pts, n, u, j,
-                         centres, Db[(j - 1) & 1], Tb[(j - 1) & 1], Db[j & 1], Tb[j & 1], L.nch);
-      HIP_TRY(hipGetLastError());
-    }
-    hipLaunchKernelGGL(kpp_select_kernel, dim3(1), dim3(kKppSelThreads), 0, s, Db[k & 1],
-                       Tb[k & 1], n, u, k - 1, centres);
-    HIP_TRY(hipGetLastError());
+  if (L.rounds) {
+    if ((st = kpp_rounds(L, pts, n, k, u, centres, labels, ws, s)) != GMM_OK) return st;
   } else {
+    double *D = at<double>(ws, L.D[0]), *T = at<double>(ws, L.T[0]);
+    const dim3 ugrid((unsigned)((L.nch + kKppUpdChunks - 1) / kKppUpdChunks));
     for (int j = 1; j < k; ++j) {
       hipLaunchKernelGGL(kpp_update_kernel, ugrid, dim3(kKppUpdThreads), 0, s, pts, n, centres,
                          j - 1, D, T, L.nch, status);
       HIP_TRY(hipGetLastError());
-      hipLaunchKernelGGL(kpp_select_kernel, dim3(1), dim3(kKppSelThreads), 0, s, D, T, n, u, j,
-                         centres);
+      hipLaunchKernelGGL(kpp_select_kernel, dim3(1), dim3(kKppSelThreads), 0, s,
+                         D, T, n, u, j, centres);
       HIP_TRY(hipGetLastError());
     }
-  }
-  if (!labels && k == 1) {  // no distances formed: check the points alone
-    hipLaunchKernelGGL(kpp_check_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       pts, n, status);
-    HIP_TRY(hipGetLastError());
-  }
-  if (labels) {
-    hipLaunchKernelGGL(kpp_label_kernel,
-                       dim3((unsigned)((n + kKppLabelThreads - 1) / kKppLabelThreads)),
-                       dim3(kKppLabelThreads), (size_t)k * 3 * sizeof(double), s, pts, n,
-                       centres, k, labels, status);
-    HIP_TRY(hipGetLastError());
+    if (!labels && k == 1) {  // no distances formed: check the points alone
+      hipLaunchKernelGGL(kpp_check_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                         pts, n, status);
+      HIP_TRY(hipGetLastError());
+    }
+    if (labels) {
+      hipLaunchKernelGGL(kpp_label_kernel,
+                         dim3((unsigned)((n + kKppLabelThreads - 1) / kKppLabelThreads)),
+                         dim3(kKppLabelThreads), (size_t)k * 3 * sizeof(double), s, pts, n,
+                         centres, k, labels, status);
+      HIP_TRY(hipGetLastError());
+    }
   }
   uint32_t bits = 0;
   HIP_TRY(gmm_host::read_words(status, 1, &bits, s));
