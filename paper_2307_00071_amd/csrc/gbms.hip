@@ -225,8 +225,8 @@ gmm_status run_meanshift(const MsLayout &L, void *ws, hipStream_t s, const float
                      max_iter, mode, weight, iters, &cnt->max_it, thr);
   HIP_TRY(hipGetLastError());
   if (thr > 0) {
-    hipLaunchKernelGGL(ms_shift4_kernel<D>, dim3((unsigned)std::min<int64_t>(n, thr)),
-                       dim3(kMsThreads), 0, s, at<float4>(ws, L.ptsS), at<int>(ws, L.start),
+    hipLaunchKernelGGL(ms_shift_block_kernel<D>, dim3((unsigned)std::min<int64_t>(n, thr)),
+                       dim3(64 * kMsSeedWaves), 0, s, at<float4>(ws, L.ptsS), at<int>(ws, L.start),
                        at<uint64_t>(ws, L.ckey), &cnt->ncells, at<uint64_t>(ws, L.hk),
                        at<int>(ws, L.hv), L.cap - 1, h, max_iter, mode, weight, iters,
                        &cnt->max_it, thr);

@@ -319,20 +319,21 @@ __global__ __launch_bounds__(kSortThreads) void ms_hash_insert_kernel(
 // and of the distance test); at most four per axis.  Slot u (4^D of them)
 // stands for the cell whose bin is congruent to the base-4 digits of u on
 // every axis; the slot is skipped when that bin is outside the range or its
-// box is farther than h from s.
+// box is farther than h from s.  With a slack (below 1/2), the same for every
+// point within slack h of s.
 template <int D>
 struct GridQuery {
   double t[D];
   int lo[D], nr[D];
-  __device__ __forceinline__ void init(const double *s, double h) {
+  __device__ __forceinline__ void init(const double *s, double h, double slack = 0.0) {
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       t[j] = s[j] / h;
-      lo[j] = (int)ceil(t[j] - 1.5 - 1e-7);
-      nr[j] = (int)floor(t[j] + 1.5 + 1e-7) - lo[j] + 1;
+      lo[j] = (int)ceil(t[j] - 1.5 - slack - 1e-7);
+      nr[j] = (int)floor(t[j] + 1.5 + slack + 1e-7) - lo[j] + 1;
     }
   }
-  __device__ __forceinline__ bool slot_key(int u, uint64_t *key) const {
+  __device__ __forceinline__ bool slot_key(int u, uint64_t *key, double slack = 0.0) const {
     int64_t k[D];
     double g2 = 0.0;
     bool ok = true;
@@ -345,7 +346,7 @@ struct GridQuery {
       const double g = fabs(t[j] - (double)k[j]) - 0.5;
       if (g > 0.0) g2 = g2 + g * g;
     }
-    ok = ok && g2 <= 1.0 + 1e-6;
+    ok = ok && g2 <= (1.0 + slack) * (1.0 + slack) * (1.0 + 1e-6);
     return ok && pack_key<D>(k, key);
   }
 };
@@ -357,7 +358,7 @@ struct GridQuery {
 // therefore sums its points in an order fixed by the cells alone: the mean
 // of an iterate depends only on the set of points within h of it.
 constexpr int kMsSerial = 16;
-constexpr int kMsBlockSeeds = 16384;   // at most this many seeds: four waves per seed
+constexpr int kMsBlockSeeds = 16384;   // at most this many seeds: a block per seed
 
 template <int D>
 __device__ __forceinline__ void ms_take(const float4 &x, bool ok, const double *s, double h2,
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(kMsThreads) void ms_shift_kernel(
   const int lane = threadIdx.x & 63;
   const int c = blockIdx.x * kMsWaves + (threadIdx.x >> 6);
   const int ncells = *ncp;
-  if (ncells <= thr) return;   // few seeds: ms_shift4_kernel takes them
+  if (ncells <= thr) return;   // few seeds: ms_shift_block_kernel takes them
   if (c >= ncells) return;     // uniform per wave
   double s[D];
   {
@@ -464,31 +465,67 @@ __global__ __launch_bounds__(kMsThreads) void ms_shift_kernel(
   }
 }
 
-// The same shift with the four waves of a block on one seed, for calls with
-// at most `thr` seeds (few seeds, large neighbourhoods: the time is the
-// slowest seed's chain of iterations).  Wave w probes the slots of rounds
-// w, w + 4, ... and walks their small cells lane by lane; the wide cells of
-// every round go to LDS in slot order and all 256 lanes walk them one
-// after another (point b + k to thread k mod 256); the four wave sums are
-// added in wave order.  Every lane's order is again fixed by the cells
-// alone.  Two barriers per iteration.
+// The same shift with a block of kMsSeedWaves waves on one seed, for calls
+// with at most `thr` seeds (few seeds, large neighbourhoods: the time is the
+// slowest seed's chain of iterations).  Thread t < 4^D holds slot t; a cell
+// is cut into pieces of 64 points; piece p of the cell in slot t is wave
+// (home(t) + p) mod kMsSeedWaves's, which takes its pieces in slot order; the
+// wave sums are added in wave order.  Every lane's order is again fixed by
+// the cells alone.
+//
+// The list of pieces is made for all positions within kMsSlack h of s and
+// serves until s has left that range (a long chain moves by little more than
+// the stop's 1e-3 h a step); the first kMsKeep pieces of a wave stay in
+// registers meanwhile.  An iteration that keeps the list has one barrier and,
+// up to kMsKeep pieces a wave, no loads.
+// Measured on clouds with the seeds of images (76,800 points, 4D; 10,972
+// seeds, 71,000 iterations, longest chain 268): the kernel 2.6 -> 1.4 ms
+// against four waves a seed that look every cell up again and load every
+// point in each iteration; 300,000 points, 3D (2,916 seeds, cap of 300
+// reached): the call 3.8 -> 2.4 ms.  Four waves a seed with this list: calls
+// 2.5 and 3.2 ms.  What is left is FP64 arithmetic (21 instructions a point)
+// and, for the bulk of the seeds, the making of the list.
+constexpr int kMsSeedWaves = 8;
+constexpr int kMsKeep = 8;
+constexpr double kMsSlack = 1.0 / 16;
+
 template <int D>
-__global__ __launch_bounds__(kMsThreads) void ms_shift4_kernel(
+__device__ __forceinline__ void ms_take_piece(const float4 &x, const double *s, double h2,
+                                              double *acc, int &in) {
+  const double xv[4] = {(double)x.x, (double)x.y, (double)x.z, (double)x.w};
+  double d[D];
+#pragma unroll
+  for (int j = 0; j < D; ++j) d[j] = xv[j] - s[j];
+  const bool t = sq_norm<D>(d) <= h2;   // (NaN: a lane past the cell's end)
+  in += __popcll(__ballot(t));
+  if (t) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) acc[j] = acc[j] + xv[j];
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kMsSeedWaves, 4) void ms_shift_block_kernel(
     const float4 *__restrict__ ptsS, const int *__restrict__ cstart,
     const uint64_t *__restrict__ ckey, const int *__restrict__ ncp,
     const uint64_t *__restrict__ hk, const int *__restrict__ hv, uint64_t mask,
     double h, int max_iter, double *__restrict__ mode, int *__restrict__ weight,
     int *__restrict__ iters, int *__restrict__ max_it, int thr) {
-  constexpr int NR = (1 << (2 * D)) / 64;   // rounds of 64 slots
-  constexpr int NW = kMsThreads / 64;
-  __shared__ int wb[NR][64], we[NR][64];    // wide cells of each round, slot order
-  __shared__ int wn[NR];
-  __shared__ double part[NW][D + 1];
+  constexpr int NW = kMsSeedWaves;
+  constexpr int NS = 1 << (2 * D), NR = NS / 64;
+  static_assert(NS <= 64 * NW && (NW & (NW - 1)) == 0, "a thread per slot");
+  __shared__ int2 list[NW][NS];   // a wave's pieces: first point, end of the cell
+  __shared__ int num[NW][NR];     // of the slots of each wave
+  __shared__ double part[2][NW][D + 1];
   const int ncells = *ncp;
   if (ncells > thr) return;                 // many seeds: ms_shift_kernel takes them
   const int c = blockIdx.x;
   if (c >= ncells) return;                  // uniform per block
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // neighbouring cells to different waves
+  const int home =
+      ((tid & 3) + 3 * (tid >> 2 & 3) + 5 * (tid >> 4 & 3) + 7 * (tid >> 6 & 3)) & (NW - 1);
   double s[D];
   {
     int64_t b[D];
@@ -498,90 +535,151 @@ __global__ __launch_bounds__(kMsThreads) void ms_shift4_kernel(
   }
   const double h2 = h * h;
   const double stop = 1e-3 * h;
+  const double reach = kMsSlack * h * (1.0 - 1e-9);
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint64_t held = kNoKey;   // the bin whose cell is [cb, ce)
+  int cb = 0, ce = 0;
   int it = 0, cnt = 0;
-  for (;;) {
-    GridQuery<D> g;
-    g.init(s, h);
-    double acc[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) acc[j] = 0.0;
-    int in = 0;
-    for (int r = w; r < NR; r += NW) {
-      int b = 0, e = 0;
+  for (bool more = true; more;) {
+    if (tid < NS) {
+      GridQuery<D> g;
+      g.init(s, h, kMsSlack);
+      int pieces = 0;
       uint64_t key;
-      if (g.slot_key(r * 64 + lane, &key)) {
-        const int id = hash_find(hk, hv, mask, key);
-        if (id >= 0) {
-          b = cstart[id];
-          e = cstart[id + 1];
+      if (g.slot_key(tid, &key, kMsSlack)) {
+        if (key != held) {
+          held = key;
+          const int id = hash_find(hk, hv, mask, key);
+          cb = id >= 0 ? cstart[id] : 0;
+          ce = id >= 0 ? cstart[id + 1] : 0;
         }
+        pieces = (ce - cb + 63) >> 6;
       }
-      const bool wide = e - b > kMsSerial;
-      if (!wide) {
-        for (int p0 = b; p0 < e; p0 += 4) {
-          float4 x[4];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) x[k] = ptsS[min(p0 + k, e - 1)];
+      for (int v = 0; v < NW; ++v) {
+        const int p = (v - home) & (NW - 1);
+        const uint64_t m = __ballot(p < pieces);
+        if (p < pieces) list[v][64 * w + __popcll(m & below)] = make_int2(cb + 64 * p, ce);
+        if (lane == 0) num[v][w] = __popcll(m);
+      }
+    }
+    __syncthreads();
+    int upto[NR];   // pieces of the slots of waves 0 .. r
 #pragma unroll
-          for (int k = 0; k < 4; ++k) ms_take<D>(x[k], p0 + k < e, s, h2, acc, in);
+    for (int r = 0; r < NR; ++r)
+      upto[r] = __builtin_amdgcn_readfirstlane(num[w][r]) + (r ? upto[r ? r - 1 : 0] : 0);
+    const int mine = upto[NR - 1];
+    // cell k of this wave: its first point here, the cell's end
+    auto cell = [&](int k) {
+      int at = k;
+#pragma unroll
+      for (int r = 0; r + 1 < NR; ++r)
+        if (k >= upto[r]) at = 64 * (r + 1) + k - upto[r];
+      const int2 u = list[w][at];
+      return make_int2(__builtin_amdgcn_readfirstlane(u.x), __builtin_amdgcn_readfirstlane(u.y));
+    };
+    // the wave's pieces in order: cell k, its piece [u.x, u.x + 64) of [.., u.y);
+    // past the last one u is a piece of no points, whose loads are in range
+    struct Cursor {
+      int k;
+      int2 u;
+    };
+    auto first = [&]() { return Cursor{0, mine > 0 ? cell(0) : make_int2(64, 1)}; };
+    auto next = [&](Cursor &q) {
+      q.u.x += 64 * NW;
+      if (q.u.x >= q.u.y && q.k < mine && ++q.k < mine) q.u = cell(q.k);
+    };
+    float4 kept[kMsKeep];
+    Cursor rest = first();
+    int nk = 0;
+    bool none[kMsKeep];
+#pragma unroll
+    for (int k = 0; k < kMsKeep; ++k) {
+      const int p = rest.u.x + lane;
+      kept[k] = ptsS[min(p, rest.u.y - 1)];
+      none[k] = p >= rest.u.y;
+      nk += rest.k < mine;
+      next(rest);
+    }
+#pragma unroll
+    for (int k = 0; k < kMsKeep; ++k)
+      if (none[k]) kept[k].x = __builtin_nanf("");
+    double s0[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) s0[j] = s[j];
+    for (;;) {
+      double acc[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) acc[j] = 0.0;
+      int in = 0;
+#pragma unroll
+      for (int k = 0; k < kMsKeep; ++k)
+        if (k < nk) {
+          // (opaque, or the conversions to FP64 are kept too: 16 registers a piece)
+          asm volatile("" : "+v"(kept[k].x), "+v"(kept[k].y), "+v"(kept[k].z), "+v"(kept[k].w));
+          ms_take_piece<D>(kept[k], s, h2, acc, in);
         }
-      }
-      const uint64_t bm = __ballot(wide);
-      if (wide) {
-        const int pos = __popcll(bm & below);
-        wb[r][pos] = b;
-        we[r][pos] = e;
-      }
-      if (lane == 0) wn[r] = __popcll(bm);
-    }
-    __syncthreads();                                                  // 1
-    for (int r = 0; r < NR; ++r) {
-      const int nw = wn[r];
-      for (int k = 0; k < nw; ++k) {
-        const int bw = wb[r][k], ew = we[r][k];
-        for (int p0 = bw + (int)threadIdx.x; p0 < ew; p0 += 4 * kMsThreads) {
-          float4 x[4];
+      for (Cursor q = rest; q.k < mine;) {
+        float4 x[4];
+        bool none[4];
+        int m = 0;
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) x[kk] = ptsS[min(p0 + kMsThreads * kk, ew - 1)];
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-            ms_take<D>(x[kk], p0 + kMsThreads * kk < ew, s, h2, acc, in);
+        for (int k = 0; k < 4; ++k) {
+          const int p = q.u.x + lane;
+          x[k] = ptsS[min(p, q.u.y - 1)];
+          none[k] = p >= q.u.y;
+          m += q.k < mine;
+          next(q);
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k < m) {
+            if (none[k]) x[k].x = __builtin_nanf("");
+            ms_take_piece<D>(x[k], s, h2, acc, in);
+          }
       }
+      double (*pt)[D + 1] = part[it & 1];
+#pragma unroll
+      for (int j = 0; j < D; ++j) acc[j] = wave_sum_f64(acc[j]);
+      if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) pt[w][j] = acc[j];
+        pt[w][D] = (double)in;
+      }
+      __syncthreads();
+      // lane j: coordinate j (the count in every lane)
+      const int col = lane < D ? lane : D;
+      double tot = pt[0][col], tin = pt[0][D];
+#pragma unroll
+      for (int v = 1; v < NW; ++v) {
+        tot = tot + pt[v][col];
+        tin += pt[v][D];
+      }
+      if (tin == 0.0) {   // uniform: every wave read the same sums
+        more = false;
+        break;
+      }
+      cnt = (int)tin;
+      const double mean = tot / tin;
+      double d[D], m[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        const double v = readlane_f64(mean, j);
+        d[j] = v - s[j];
+        s[j] = v;
+        m[j] = v - s0[j];
+      }
+      const double q = sq_norm<D>(d);
+      // (the root only where it can decide)
+      if ((q <= stop * stop * (1.0 + 1e-9) + 1e-300 && sqrt(q) <= stop) || it == max_iter) {
+        more = false;
+        break;
+      }
+      ++it;
+      if (!(sq_norm<D>(m) <= reach * reach)) break;   // a new list
     }
-#pragma unroll
-    for (int j = 0; j < D; ++j) acc[j] = wave_sum_f64(acc[j]);
-    in = wave_sum_i32(in);
-    if (lane == 0) {
-#pragma unroll
-      for (int j = 0; j < D; ++j) part[w][j] = acc[j];
-      part[w][D] = (double)in;
-    }
-    __syncthreads();                                                  // 2
-    double tot[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) tot[j] = part[0][j];
-    int tin = (int)part[0][D];
-#pragma unroll
-    for (int v = 1; v < NW; ++v) {
-#pragma unroll
-      for (int j = 0; j < D; ++j) tot[j] = tot[j] + part[v][j];
-      tin += (int)part[v][D];
-    }
-    if (tin == 0) break;   // uniform: every thread read the same sums
-    cnt = tin;
-    double d[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const double v = tot[j] / (double)tin;
-      d[j] = v - s[j];
-      s[j] = v;
-    }
-    if (sqrt(sq_norm<D>(d)) <= stop || it == max_iter) break;
-    ++it;
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
 #pragma unroll
     for (int j = 0; j < D; ++j) mode[(size_t)c * D + j] = s[j];
     weight[c] = cnt;
