@@ -64,7 +64,7 @@ struct MsLayout {
   size_t ptsS;            // sorted points (float4)
   size_t start;           // cell starts, n + 1
   size_t ckey;            // cell keys
-  size_t hk, hv;          // hash table
+  size_t hk, hv, hs;      // hash table; range starts of the mode grid
   size_t mode, weight, iters, status;
   size_t total;
 };
@@ -83,7 +83,7 @@ MsLayout ms_layout(int64_t n, int d) {
   };
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
   L.cnt = take(sizeof(MsCounters));
-  L.rounds = take((kRoundBatch + 1) * sizeof(unsigned));
+  L.rounds = take((2 * kRoundBatch + 1) * sizeof(unsigned));
   L.klo = take(nn * 4);
   L.khi = take(nn * 4);
   L.vals = take(nn * 4);
@@ -99,6 +99,7 @@ MsLayout ms_layout(int64_t n, int d) {
   L.ckey = take(nn * 8);
   L.hk = take(L.cap * 8);
   L.hv = take(L.cap * 4);
+  L.hs = take(L.cap * 4);
   L.mode = take(nn * d * 8);
   L.weight = take(nn * 4);
   L.iters = take(nn * 4);
@@ -205,7 +206,7 @@ gmm_status run_meanshift(const MsLayout &L, void *ws, hipStream_t s, const float
   if ((st = sort64(L, ws, s, n)) != GMM_OK) return st;
   hipLaunchKernelGGL(ms_sorted_kernel<D>, dim3(blocks(n, kSortThreads)), dim3(kSortThreads), 0,
                      s, at<unsigned>(ws, L.klo), at<unsigned>(ws, L.khi),
-                     at<unsigned>(ws, L.vA), pts, (const int *)nullptr, n,
+                     at<unsigned>(ws, L.vA), pts, n,
                      at<uint64_t>(ws, L.keys), at<float4>(ws, L.ptsS));
   HIP_TRY(hipGetLastError());
   if ((st = build_grid(L, ws, s, n, &cnt->ncells)) != GMM_OK) return st;
@@ -233,46 +234,45 @@ gmm_status run_meanshift(const MsLayout &L, void *ws, hipStream_t s, const float
     HIP_TRY(hipGetLastError());
   }
 
-  // ---- the mode grid over the same buffers; perm2 (sorted -> seed) in vA
-  hipLaunchKernelGGL(ms_mode_key_kernel<D>, dim3(blocks(n, kSortThreads)), dim3(kSortThreads),
-                     0, s, mode, weight, &cnt->ncells, n, h, at<unsigned>(ws, L.klo),
-                     at<unsigned>(ws, L.khi), at<unsigned>(ws, L.vals));
+  // ---- the mode grid; slot and rank of a mode in klo and khi, the modes by
+  // slot in vA
+  uint64_t *hk = at<uint64_t>(ws, L.hk);
+  int *hcount = at<int>(ws, L.hv), *hstart = at<int>(ws, L.hs), *perm2 = at<int>(ws, L.vA);
+  unsigned *slot = at<unsigned>(ws, L.klo);
+  int *rank = at<int>(ws, L.khi);
+  const dim3 gn(blocks(n, kSortThreads)), tn(kSortThreads);
+  hipLaunchKernelGGL(ms_mode_clear_kernel, dim3(blocks((int64_t)L.cap, kSortThreads)), tn, 0, s,
+                     hk, hcount, L.cap, &cnt->nmodes);
   HIP_TRY(hipGetLastError());
-  if ((st = sort64(L, ws, s, n)) != GMM_OK) return st;
-  hipLaunchKernelGGL(ms_sorted_kernel<D>, dim3(blocks(n, kSortThreads)), dim3(kSortThreads), 0,
-                     s, at<unsigned>(ws, L.klo), at<unsigned>(ws, L.khi),
-                     at<unsigned>(ws, L.vA), (const float *)nullptr, (const int *)nullptr, n,
-                     at<uint64_t>(ws, L.keys), (float4 *)nullptr);
+  hipLaunchKernelGGL(ms_mode_insert_kernel<D>, gn, tn, 0, s, mode, weight, &cnt->ncells, h, hk,
+                     hcount, L.cap - 1, slot, rank, status);
   HIP_TRY(hipGetLastError());
-  if ((st = build_grid(L, ws, s, n, &cnt->nmodes)) != GMM_OK) return st;
+  hipLaunchKernelGGL(ms_mode_range_kernel, gn, tn, 0, s, &cnt->ncells, slot, rank, hcount, hstart,
+                     &cnt->nmodes);
+  HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(ms_mode_fill_kernel, gn, tn, 0, s, &cnt->ncells, slot, rank, hstart, perm2);
+  HIP_TRY(hipGetLastError());
 
-  // ---- merge rounds, kRoundBatch launches per check of the last count
-  hipLaunchKernelGGL(ms_status_init_kernel, dim3(blocks(n, kSortThreads)), dim3(kSortThreads), 0,
-                     s, weight, &cnt->ncells, status);
-  HIP_TRY(hipGetLastError());
+  // ---- merge, kRoundBatch launches per check of the last count
   int rounds = 0;
-  for (int batch = 0;; ++batch) {
-    hipLaunchKernelGGL(ms_round_clear_kernel, dim3(1), dim3(64), 0, s, rc, batch == 0 ? 1 : 0);
+  for (int64_t launches = 0;;) {
+    hipLaunchKernelGGL(ms_round_clear_kernel, dim3(1), dim3(64), 0, s, rc, launches == 0 ? 1 : 0);
     HIP_TRY(hipGetLastError());
     for (int r = 1; r <= kRoundBatch; ++r) {
-      hipLaunchKernelGGL(ms_merge_round_kernel<D>, dim3(blocks(n, kMsWaves)), dim3(kMsThreads), 0,
-                         s, mode, weight, &cnt->ncells, at<unsigned>(ws, L.vA),
-                         at<int>(ws, L.start), at<uint64_t>(ws, L.hk), at<int>(ws, L.hv),
-                         L.cap - 1, h, status, rc, r);
+      hipLaunchKernelGGL(ms_merge_kernel<D>,
+                         dim3(std::min(blocks(n, kMsWaves), (unsigned)kMergeBlocks)),
+                         dim3(kMsThreads), 0, s, mode, weight, &cnt->ncells, perm2, hstart, hcount,
+                         hk, L.cap - 1, h, status, rc, r);
       HIP_TRY(hipGetLastError());
     }
-    unsigned hc[kRoundBatch + 1];
-    static_assert(kRoundBatch + 1 <= gmm_host::kReadWords, "one read");
-    HIP_TRY(gmm_host::read_words(rc, kRoundBatch + 1, hc, s));
-    int r = 1;
-    while (r <= kRoundBatch && hc[r] != 0u) ++r;
-    if (r <= kRoundBatch) {
-      rounds += r;
-      break;
-    }
-    rounds += kRoundBatch;
-    if (rounds > n + kRoundBatch)   // each round decides a mode: cannot happen
-      return fail(GMM_ERR_DEVICE, "merge did not finish after %d rounds", rounds);
+    unsigned hc[2 * kRoundBatch + 1];
+    static_assert(2 * kRoundBatch + 1 <= gmm_host::kReadWords, "one read");
+    HIP_TRY(gmm_host::read_words(rc, 2 * kRoundBatch + 1, hc, s));
+    for (int r = 1; r <= kRoundBatch; ++r) rounds += (int)hc[kRoundBatch + r];
+    if (hc[kRoundBatch] == 0u) break;
+    launches += kRoundBatch;
+    if (launches > n + kRoundBatch)   // each launch decides a mode: cannot happen
+      return fail(GMM_ERR_DEVICE, "merge did not finish after %d passes", rounds);
   }
 
   // ---- the kept modes in seed order

@@ -26,9 +26,9 @@
 //     that reach the same neighbourhood get bitwise the same mean;
 //   * the merge never sorts the modes: mode i is kept iff no kept mode that
 //     precedes it lies within h, so it needs only the predecessors within h
-//     (a second grid, over the modes).  Rounds decide, in place, every mode
-//     whose predecessors within h are all decided; each round decides at
-//     least the first undecided mode of the order, so the rounds end.
+//     (a second grid, over the modes).  Passes decide, in place, every mode
+//     whose predecessors within h are all decided; each pass decides at
+//     least the first undecided mode of the order, so the passes end.
 // All arithmetic that decides a neighbourhood, a bin, a stop or a merge is
 // FP64 with every product and sum rounded on its own (no contraction), in the
 // order ((d0^2 + d1^2) + d2^2) + d3^2.
@@ -54,7 +54,7 @@ using gmm_dev::kSortThreads;
 constexpr int kMsThreads = 256;
 constexpr int kMsWaves = kMsThreads / 64;   // seeds (or modes) per block
 constexpr uint64_t kNoKey = ~0ull;          // empty hash slot; no real key has it
-constexpr int kRoundBatch = 16;             // merge rounds per host check
+constexpr int kRoundBatch = 2;              // merge launches per host check
 
 // device status bits
 constexpr uint32_t kMsNonFinite = 1u;
@@ -158,27 +158,6 @@ __global__ __launch_bounds__(kSortThreads) void ms_point_key_kernel(
   vals[i] = (unsigned)i;
 }
 
-// Key of mode i (bins of the mode grid) for i < n items; all ones for a
-// dropped seed and for the items past the seed count *nsp.
-template <int D>
-__global__ __launch_bounds__(kSortThreads) void ms_mode_key_kernel(
-    const double *__restrict__ mode, const int *__restrict__ weight,
-    const int *__restrict__ nsp, int64_t n, double h, unsigned *__restrict__ klo,
-    unsigned *__restrict__ khi, unsigned *__restrict__ vals) {
-  const int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x;
-  if (i >= n) return;
-  uint64_t key = kNoKey;
-  if (i < *nsp && weight[i] > 0) {
-    int64_t b[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) b[j] = (int64_t)rint(mode[(size_t)i * D + j] / h);
-    if (!pack_key<D>(b, &key)) key = kNoKey;   // cannot happen: modes are means of points
-  }
-  klo[i] = (unsigned)key;
-  khi[i] = (unsigned)(key >> 32);
-  vals[i] = (unsigned)i;
-}
-
 // out[i] = in[perm[i]] (32-bit words)
 __global__ __launch_bounds__(kSortThreads) void ms_gather_u32_kernel(
     const unsigned *__restrict__ in, const unsigned *__restrict__ perm,
@@ -188,22 +167,18 @@ __global__ __launch_bounds__(kSortThreads) void ms_gather_u32_kernel(
   if (i < n) out[i] = in[perm[i]];
 }
 
-// Sorted 64-bit keys and, for the points, the sorted float4 copies.
+// Sorted 64-bit keys and the points' sorted float4 copies.
 template <int D>
 __global__ __launch_bounds__(kSortThreads) void ms_sorted_kernel(
     const unsigned *__restrict__ klo, const unsigned *__restrict__ khi,
-    const unsigned *__restrict__ perm, const float *__restrict__ pts,
-    const int *__restrict__ np, int64_t nmax, uint64_t *__restrict__ keys,
-    float4 *__restrict__ ptsS) {
+    const unsigned *__restrict__ perm, const float *__restrict__ pts, int64_t n,
+    uint64_t *__restrict__ keys, float4 *__restrict__ ptsS) {
   const int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x;
-  const int64_t n = np ? (int64_t)*np : nmax;
   if (i >= n) return;
   const unsigned p = perm[i];
   keys[i] = ((uint64_t)khi[p] << 32) | klo[p];
-  if (ptsS) {
-    const float *x = pts + (size_t)p * D;
-    ptsS[i] = make_float4(x[0], x[1], x[2], D == 4 ? x[3] : 0.0f);
-  }
+  const float *x = pts + (size_t)p * D;
+  ptsS[i] = make_float4(x[0], x[1], x[2], D == 4 ? x[3] : 0.0f);
 }
 
 // ------------------------------------------------- flags and their scan
@@ -292,7 +267,7 @@ __global__ __launch_bounds__(kSortThreads) void ms_hash_clear_kernel(
   if (i < cap) hk[i] = kNoKey;
 }
 
-// Cell c's key into the table (the all-ones key of dropped seeds is not).
+// Cell c's key into the table.
 __global__ __launch_bounds__(kSortThreads) void ms_hash_insert_kernel(
     const uint64_t *__restrict__ ckey, const int *__restrict__ ncp,
     uint64_t *__restrict__ hk, int *__restrict__ hv, uint64_t mask) {
@@ -690,19 +665,82 @@ __global__ __launch_bounds__(64 * kMsSeedWaves, 4) void ms_shift_block_kernel(
 
 // ------------------------------------------------------------------ merge
 // status: 0 undecided, 1 kept, 2 removed by a kept mode, 3 dropped seed.
-__global__ __launch_bounds__(kSortThreads) void ms_status_init_kernel(
-    const int *__restrict__ weight, const int *__restrict__ nsp, int *__restrict__ status) {
+//
+// The grid over the modes needs no order, so it is not sorted: every mode
+// takes a place in its cell's hash slot, the slots take ranges, and the modes
+// are written to them (three short launches; sorted like the points' it took
+// thirty, 190 us at 76,800 points).
+__global__ __launch_bounds__(kSortThreads) void ms_mode_clear_kernel(
+    uint64_t *__restrict__ hk, int *__restrict__ hcount, uint64_t cap, int *__restrict__ used) {
+  const uint64_t i = (uint64_t)blockIdx.x * kSortThreads + threadIdx.x;
+  if (i == 0) *used = 0;
+  if (i < cap) {
+    hk[i] = kNoKey;
+    hcount[i] = 0;
+  }
+}
+
+// slot[i], rank[i]: mode i's place; rank -1 for a dropped seed.
+template <int D>
+__global__ __launch_bounds__(kSortThreads) void ms_mode_insert_kernel(
+    const double *__restrict__ mode, const int *__restrict__ weight,
+    const int *__restrict__ nsp, double h, uint64_t *__restrict__ hk, int *__restrict__ hcount,
+    uint64_t mask, unsigned *__restrict__ slot, int *__restrict__ rank,
+    int *__restrict__ status) {
   const int i = blockIdx.x * kSortThreads + threadIdx.x;
-  if (i < *nsp) status[i] = weight[i] > 0 ? 0 : 3;
+  if (i >= *nsp) return;
+  const bool live = weight[i] > 0;
+  status[i] = live ? 0 : 3;
+  rank[i] = -1;
+  int64_t b[D];
+  uint64_t key;
+#pragma unroll
+  for (int j = 0; j < D; ++j) b[j] = (int64_t)rint(mode[(size_t)i * D + j] / h);
+  if (!live || !pack_key<D>(b, &key)) return;   // (modes are means of points: in range)
+  uint64_t s = mix64(key) & mask;
+  for (;;) {
+    const unsigned long long prev =
+        atomicCAS(reinterpret_cast<unsigned long long *>(hk + s),
+                  (unsigned long long)kNoKey, (unsigned long long)key);
+    if (prev == (unsigned long long)kNoKey || prev == (unsigned long long)key) break;
+    s = (s + 1) & mask;
+  }
+  slot[i] = (unsigned)s;
+  rank[i] = atomicAdd(&hcount[s], 1);
+}
+
+// The first mode of a slot takes the slot's range.
+__global__ __launch_bounds__(kSortThreads) void ms_mode_range_kernel(
+    const int *__restrict__ nsp, const unsigned *__restrict__ slot, const int *__restrict__ rank,
+    const int *__restrict__ hcount, int *__restrict__ hstart, int *__restrict__ used) {
+  __shared__ unsigned wsum[kSortThreads / 64];
+  __shared__ int base;
+  const int i = blockIdx.x * kSortThreads + threadIdx.x;
+  if ((int)blockIdx.x * kSortThreads >= *nsp) return;   // uniform
+  const bool take = i < *nsp && rank[i] == 0;
+  unsigned tot = 0;
+  const unsigned off =
+      gmm_dev::block_exclusive_scan256(take ? (unsigned)hcount[slot[i]] : 0u, wsum, &tot);
+  if (threadIdx.x == 0) base = atomicAdd(used, (int)tot);
+  __syncthreads();
+  if (take) hstart[slot[i]] = base + (int)off;
+}
+
+__global__ __launch_bounds__(kSortThreads) void ms_mode_fill_kernel(
+    const int *__restrict__ nsp, const unsigned *__restrict__ slot, const int *__restrict__ rank,
+    const int *__restrict__ hstart, int *__restrict__ perm2) {
+  const int i = blockIdx.x * kSortThreads + threadIdx.x;
+  if (i < *nsp && rank[i] >= 0) perm2[hstart[slot[i]] + rank[i]] = i;
 }
 
 // cnt[0] = carry, cnt[1 .. kRoundBatch] = 0 (carry: the undecided count of
-// the previous batch's last round, or 1 before the first round).
+// the previous batch's last launch, or 1 before the first); the passes of
+// each launch behind them.
 __global__ void ms_round_clear_kernel(unsigned *__restrict__ cnt, int first) {
   const int t = threadIdx.x;
   const unsigned carry = first ? 1u : cnt[kRoundBatch];
   __syncthreads();
-  if (t <= kRoundBatch) cnt[t] = (t == 0) ? carry : 0u;
+  if (t <= 2 * kRoundBatch) cnt[t] = (t == 0) ? carry : 0u;
 }
 
 // Does mode j come before mode i in the merge order?
@@ -716,66 +754,150 @@ __device__ __forceinline__ bool precedes(int j, int wj, const double *mj, int i,
   return j < i;
 }
 
-// One merge round, one wave per undecided mode: removed if a kept
-// predecessor lies within h, kept if every predecessor within h is decided
-// and none is kept, else counted in cnt[round].
+// Merge passes, one wave per undecided mode (wave k has modes k, k + waves,
+// ...): a mode is removed if a kept predecessor lies within h, kept if every
+// predecessor within h is decided and none is kept, else looked at again in
+// the next pass.  A launch ends when its modes are decided or after
+// kMergePasses (no wave waits for a block that has not started); what is
+// left is counted in cnt[launch].
+//
+// The first pass spreads the modes of all the cells in reach over the lanes,
+// and keeps the undecided predecessors of a wave's first kMergeOwn modes (up
+// to kMergeList each) in LDS: a later pass reads their status alone.  One
+// launch a round, a lane per cell, took 155, 89, 37, ... 14 us for the 17
+// rounds of 10,972 modes (600 us with the idle launches to the host's check);
+// this takes 73 us.
+constexpr int kMergeBlocks = 1024;
+constexpr int kMergePasses = 64;
+constexpr int kMergeOwn = 4;
+constexpr int kMergeList = 128;
+
+__device__ __forceinline__ int ms_status_load(const int *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int D>
-__global__ __launch_bounds__(kMsThreads) void ms_merge_round_kernel(
+__global__ __launch_bounds__(kMsThreads) void ms_merge_kernel(
     const double *__restrict__ mode, const int *__restrict__ weight,
-    const int *__restrict__ nsp, const unsigned *__restrict__ perm2,
-    const int *__restrict__ mstart, const uint64_t *__restrict__ hk,
-    const int *__restrict__ hv, uint64_t mask, double h, int *status,
-    unsigned *__restrict__ cnt, int round) {
-  if (cnt[round - 1] == 0u) return;   // every mode decided already
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kMsWaves + (threadIdx.x >> 6);
-  if (i >= *nsp) return;
-  volatile int *vst = status;
-  if (vst[i] != 0) return;
-  double mi[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) mi[k] = mode[(size_t)i * D + k];
-  const int wi = weight[i];
+    const int *__restrict__ nsp, const int *__restrict__ perm2,
+    const int *__restrict__ hstart, const int *__restrict__ hcount,
+    const uint64_t *__restrict__ hk, uint64_t mask, double h, int *status,
+    unsigned *__restrict__ cnt, int launch) {
+  __shared__ int held[kMsWaves][kMergeOwn][kMergeList];
+  __shared__ int nheld[kMsWaves][kMergeOwn];   // -1: too many
+  if (cnt[launch - 1] == 0u) return;   // every mode decided already
+  const int ns = *nsp;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const double h2 = h * h;
-  GridQuery<D> g;
-  g.init(mi, h);
-  bool kept_pred = false, open_pred = false;
-  for (int u0 = 0; u0 < (1 << (2 * D)); u0 += 64) {
-    uint64_t key;
-    if (!g.slot_key(u0 + lane, &key)) continue;
-    const int id = hash_find(hk, hv, mask, key);
-    if (id < 0) continue;
-    const int p1 = mstart[id + 1];
-    for (int p = mstart[id]; p < p1; ++p) {
-      const int j = (int)perm2[p];
-      if (j == i) continue;
-      const int st = vst[j];
-      if (st >= 2) continue;
-      double mj[D], d[D];
+  const int stride = (int)gridDim.x * kMsWaves;
+  unsigned left = 0;
+  int pass = 0;
+  for (; pass < kMergePasses; ++pass) {
+    left = 0;
+    int own = 0;
+    for (int64_t ii = (int64_t)blockIdx.x * kMsWaves + w; ii < ns; ii += stride, ++own) {
+      const int i = (int)ii;
+      if (ms_status_load(status + i) != 0) continue;
+      bool kept = false, open = false;
+      const int nl = pass > 0 && own < kMergeOwn ? nheld[w][own] : -1;
+      if (nl >= 0) {
+        for (int q = lane; q < nl; q += 64) {
+          const int st = ms_status_load(status + held[w][own][q]);
+          kept = kept || st == 1;
+          open = open || st == 0;
+        }
+      } else {
+        double mi[D];
 #pragma unroll
-      for (int k = 0; k < D; ++k) {
-        mj[k] = mode[(size_t)j * D + k];
-        d[k] = mi[k] - mj[k];
+        for (int k = 0; k < D; ++k) mi[k] = mode[(size_t)i * D + k];
+        const int wi = weight[i];
+        GridQuery<D> g;
+        g.init(mi, h);
+        int listed = 0;   // uniform
+        for (int u0 = 0; u0 < (1 << (2 * D)); u0 += 64) {
+          int b = 0, c = 0;
+          uint64_t key;
+          if (g.slot_key(u0 + lane, &key)) {
+            uint64_t s = mix64(key) & mask;
+            for (;;) {
+              const uint64_t k = hk[s];
+              if (k == key) {
+                b = hstart[s];
+                c = hcount[s];
+                break;
+              }
+              if (k == kNoKey) break;
+              s = (s + 1) & mask;
+            }
+          }
+          int upto = c;   // inclusive running count
+          for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += o;
+          }
+          const int total = __builtin_amdgcn_readlane(upto, 63);
+          for (int q0 = 0; q0 < total; q0 += 64) {
+            const int q = q0 + lane;
+            int o = 0;   // the slot of the q-th mode
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)
+              if (__shfl(upto, o + step - 1, 64) <= q) o += step;
+            o &= 63;   // (q past the end)
+            const int p = __shfl(b, o, 64) + q - (__shfl(upto, o, 64) - __shfl(c, o, 64));
+            bool pre = false;
+            int j = 0;
+            if (q < total) {
+              j = perm2[p];
+              const int st = j == i ? 2 : ms_status_load(status + j);
+              if (st < 2) {
+                double mj[D], d[D];
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                  mj[k] = mode[(size_t)j * D + k];
+                  d[k] = mi[k] - mj[k];
+                }
+                if (sq_norm<D>(d) <= h2 && precedes<D>(j, weight[j], mj, i, wi, mi)) {
+                  kept = kept || st == 1;
+                  pre = st == 0;
+                }
+              }
+            }
+            open = open || pre;
+            const uint64_t m = __ballot(pre);
+            if (own < kMergeOwn) {
+              const int at = listed + __popcll(m & below);
+              if (pre && at < kMergeList) held[w][own][at] = j;
+            }
+            listed += __popcll(m);
+          }
+          if (__ballot(kept)) break;
+        }
+        if (own < kMergeOwn && lane == 0) nheld[w][own] = listed <= kMergeList ? listed : -1;
+        __builtin_amdgcn_wave_barrier();   // the list is read by other lanes of the wave
       }
-      if (sq_norm<D>(d) <= h2 && precedes<D>(j, weight[j], mj, i, wi, mi)) {
-        if (st == 1) kept_pred = true;
-        else open_pred = true;
+      const bool any_kept = __ballot(kept) != 0ull, any_open = __ballot(open) != 0ull;
+      if (!any_kept && any_open) {
+        ++left;
+        continue;
       }
+      if (lane == 0)
+        __hip_atomic_store(status + i, any_kept ? 2 : 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (left == 0) break;
   }
-  const bool kept = __ballot(kept_pred) != 0ull;
-  const bool open = __ballot(open_pred) != 0ull;
   if (lane == 0) {
-    if (kept) vst[i] = 2;
-    else if (!open) vst[i] = 1;
-    else atomicAdd(&cnt[round], 1u);
+    if (left) atomicAdd(&cnt[launch], left);
+    const unsigned passes = (unsigned)(pass < kMergePasses ? pass + 1 : pass);
+    if (passes > 1 || blockIdx.x == 0) atomicMax(&cnt[kRoundBatch + launch], passes);
   }
 }
 
 // The status word and the counters to the host's info block.
 struct MsCounters {
   int ncells;    // seeds
-  int nmodes;    // cells of the mode grid
+  int nmodes;    // modes in the mode grid
   int kept;      // K
   int max_it;
   uint32_t status;
