@@ -624,6 +624,8 @@ __global__ __launch_bounds__(kUpdThreads) void cond_prep_kernel(
   __shared__ double scratch[2 * kUpdThreads / 64];
   const int b = threadIdx.x;
   const bool act = b < K;
+  if (b == 0) *status = 0u;
+  __syncthreads();
   double cb = -INFINITY;
   float *q = cb_out + (size_t)b * kCond;
   if (act) {
@@ -670,84 +672,137 @@ __device__ __forceinline__ float cond_logterm(const float *__restrict__ q, float
   return fmaf(-z2, z2, l);
 }
 
-// One thread per location: beta_b = softmax of the marginal log terms,
-// E = sum beta m_b, V = sum beta (v_b + (m_b - E)^2), with FP64 sums.
-__global__ __launch_bounds__(256) void cond4_kernel(const float *__restrict__ locs, int64_t M,
-                                                    const float *__restrict__ cb, int K,
-                                                    float *__restrict__ Eout,
-                                                    float *__restrict__ Vout,
-                                                    uint32_t *status) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  const float x = locs[3 * i], y = locs[3 * i + 1], z = locs[3 * i + 2];
-  if (!(isfinite(x) && isfinite(y) && isfinite(z))) {
-    set_status(status, kStNonFinite);
-    Eout[i] = NAN;
-    Vout[i] = NAN;
-    return;
-  }
-  float shift = 0.0f;
-  double s = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int pass = 0; pass < 2; ++pass) {
-    s = 0.0; s1 = 0.0; s2 = 0.0;
-    for (int b = 0; b < K; ++b) {
-      const float *q = cb + (size_t)b * kCond;
-      float m;
-      const float l = cond_logterm(q, x, y, z, m);
-      const double e = (double)__builtin_amdgcn_exp2f(l - shift);
-      s += e;
-      s1 += e * (double)m;
-      s2 = fma(e, (double)q[14] + (double)m * (double)m, s2);
+// beta_b = softmax of the marginal log terms, E = sum beta m_b,
+// V = sum beta (v_b + (m_b - E)^2), with FP64 sums.  A block has 64 locations
+// and kCondWaves waves, each with a range of the components; the sums of the
+// ranges are added in wave order.  Bound by the latency of the components'
+// scalar loads: 10 us at an image's 76,800 locations, K = 100; 38 us with a
+// thread per location (one wave a SIMD).
+constexpr int kCondWaves = 4;
+constexpr int64_t kCondBlocks = 1 << 20;   // then blocks take several groups
+
+__global__ __launch_bounds__(64 * kCondWaves) void cond4_kernel(
+    const float *__restrict__ locs, int64_t M, const float *__restrict__ cb, int K,
+    float *__restrict__ Eout, float *__restrict__ Vout, uint32_t *status) {
+  __shared__ double sums[kCondWaves][3][64];
+  __shared__ float top[kCondWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lo = (w * K) / kCondWaves, hi = ((w + 1) * K) / kCondWaves;
+  for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < M; i0 += (int64_t)gridDim.x * 64) {
+    const int64_t i = i0 + lane;
+    float x = 0.0f, y = 0.0f, z = 0.0f;
+    if (i < M) {
+      x = locs[3 * i];
+      y = locs[3 * i + 1];
+      z = locs[3 * i + 2];
     }
-    if (s >= 0x1p-100) break;
-    // far from every component: redo with this location's own maximum
-    float mx = -INFINITY;
-    for (int b = 0; b < K; ++b) {
-      float m;
-      mx = fmaxf(mx, cond_logterm(cb + (size_t)b * kCond, x, y, z, m));
+    const bool fin = isfinite(x) && isfinite(y) && isfinite(z);
+    float shift = 0.0f;
+    double s = 0.0, s1 = 0.0, s2 = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+      s = 0.0; s1 = 0.0; s2 = 0.0;
+#pragma unroll 4
+      for (int b = lo; b < hi; ++b) {
+        const float *q = cb + (size_t)b * kCond;
+        float m;
+        const float l = cond_logterm(q, x, y, z, m);
+        const double e = (double)__builtin_amdgcn_exp2f(l - shift);
+        s += e;
+        s1 += e * (double)m;
+        s2 = fma(e, (double)q[14] + (double)m * (double)m, s2);
+      }
+      sums[w][0][lane] = s;
+      sums[w][1][lane] = s1;
+      sums[w][2][lane] = s2;
+      __syncthreads();
+      s = sums[0][0][lane]; s1 = sums[0][1][lane]; s2 = sums[0][2][lane];
+#pragma unroll
+      for (int v = 1; v < kCondWaves; ++v) {
+        s += sums[v][0][lane];
+        s1 += sums[v][1][lane];
+        s2 += sums[v][2][lane];
+      }
+      // far from every component: redo with this location's own maximum
+      const bool far = pass == 0 && i < M && fin && !(s >= 0x1p-100);
+      if (__ballot(far) == 0ull) break;   // the same locations in every wave
+      float mx = -INFINITY;
+      for (int b = lo; b < hi; ++b) {
+        float m;
+        mx = fmaxf(mx, cond_logterm(cb + (size_t)b * kCond, x, y, z, m));
+      }
+      top[w][lane] = mx;
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < kCondWaves; ++v) mx = fmaxf(mx, top[v][lane]);
+      if (far) shift = mx;
     }
-    shift = mx;
+    if (w == 0 && i < M) {
+      if (fin) {
+        const double E = s1 / s;
+        // variance of the mixture, centred in FP64 (the raw second moment
+        // and E^2 are both O(E^2))
+        double V = s2 / s - E * E;
+        if (V < 0.0) V = 0.0;
+        Eout[i] = (float)E;
+        Vout[i] = (float)V;
+      } else {
+        set_status(status, kStNonFinite);
+        Eout[i] = NAN;
+        Vout[i] = NAN;
+      }
+    }
+    __syncthreads();   // the sums are read
   }
-  const double E = s1 / s;
-  // variance of the mixture, centred in FP64 (the raw second moment and
-  // E^2 are both O(E^2))
-  double V = s2 / s - E * E;
-  if (V < 0.0) V = 0.0;
-  Eout[i] = (float)E;
-  Vout[i] = (float)V;
 }
 
 // ----------------------------------------------------------- joint sampling
-// run[b] = w_0 + ... + w_b in double, component order (one thread), and the
-// FP64 Cholesky factors (lower, 10 values) per component.
+// run[b] = w_0 + ... + w_b in double, component order (one thread, from
+// LDS), and the FP64 Cholesky factors (lower, 10 values) per component by the
+// other waves.
 __global__ __launch_bounds__(256) void sample_prep_kernel(const float *__restrict__ w,
                                                           const float *__restrict__ cov, int K,
                                                           double *__restrict__ run,
                                                           double *__restrict__ Lf,
                                                           int *__restrict__ last,
                                                           uint32_t *status) {
+  __shared__ float sw[GMM_MAX_K];
+  __shared__ uint32_t bits;
+  if (threadIdx.x == 0) bits = 0u;
+  __syncthreads();
   for (int b = threadIdx.x; b < K; b += blockDim.x) {
-    double C[10], L[10], P[10];
-    for (int r = 0; r < 4; ++r)
-      for (int c = 0; c <= r; ++c) C[tri(r, c)] = cov[16 * b + 4 * r + c];
-    if (!chol_inv4(C, L, P)) {
-      set_status(status, kStNotSpd);
-      for (int j = 0; j < 10; ++j) L[j] = NAN;
-    }
-    for (int j = 0; j < 10; ++j) Lf[10 * b + j] = L[j];
-    if (!(w[b] >= 0.0f) || !isfinite(w[b])) set_status(status, kStBadArg);
+    const float v = w[b];
+    sw[b] = v;
+    if (!(v >= 0.0f) || !isfinite(v)) atomicOr(&bits, kStBadArg);
   }
+  __syncthreads();
   if (threadIdx.x == 0) {
     double acc = 0.0;
     int lp = -1;
+#pragma unroll 8
     for (int b = 0; b < K; ++b) {
-      acc += (double)w[b];
+      acc += (double)sw[b];
       run[b] = acc;
-      if (w[b] > 0.0f) lp = b;
+      if (sw[b] > 0.0f) lp = b;
     }
-    if (lp < 0) set_status(status, kStBadArg);
+    if (lp < 0) atomicOr(&bits, kStBadArg);
     *last = lp < 0 ? 0 : lp;
   }
+  if (threadIdx.x >= 64)
+    for (int b = threadIdx.x - 64; b < K; b += blockDim.x - 64) {
+      double C[10], L[10], P[10];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c <= r; ++c) C[tri(r, c)] = cov[16 * b + 4 * r + c];
+      if (!chol_inv4(C, L, P)) {
+        atomicOr(&bits, kStNotSpd);
+        for (int j = 0; j < 10; ++j) L[j] = NAN;
+      }
+      for (int j = 0; j < 10; ++j) Lf[10 * b + j] = L[j];
+    }
+  __syncthreads();
+  if (threadIdx.x == 0) *status = bits;
 }
 
 // One thread per sample: the first component whose running weight sum

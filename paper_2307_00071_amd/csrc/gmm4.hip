@@ -593,13 +593,11 @@ gmm_status gmm4_color_conditional(const float *locs, int64_t m, int32_t k, const
   if (st != GMM_OK) return st;
   uint32_t *status = at<uint32_t>(ws, 0);
   float *cb = at<float>(ws, align256(256));
-  hipLaunchKernelGGL(init4_kernel, dim3(1), dim3(64), 0, s, status, nullptr, 0);
-  HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(cond_prep_kernel, dim3(1), dim3(kUpdThreads), 0, s, w, mu, cov, k, cb,
                      status);
   HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(cond4_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, locs, m,
-                     cb, k, expected, variance, status);
+  hipLaunchKernelGGL(cond4_kernel, dim3((unsigned)std::min((m + 63) / 64, kCondBlocks)),
+                     dim3(64 * kCondWaves), 0, s, locs, m, cb, k, expected, variance, status);
   HIP_TRY(hipGetLastError());
   return GMM_OK;
 }
@@ -628,8 +626,6 @@ gmm_status gmm4_joint_dist_sample(int32_t k, const float *w, const float *mu, co
   double *run = at<double>(ws, o); o = align256(o + (size_t)k * sizeof(double));
   double *Lf = at<double>(ws, o); o = align256(o + (size_t)k * 10 * sizeof(double));
   int *last = at<int>(ws, o);
-  hipLaunchKernelGGL(init4_kernel, dim3(1), dim3(64), 0, s, status, nullptr, 0);
-  HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(sample_prep_kernel, dim3(1), dim3(256), 0, s, w, cov, k, run, Lf, last,
                      status);
   HIP_TRY(hipGetLastError());
