@@ -683,7 +683,7 @@ def registration(reps=20, cpu=True):
                       "evaluated_pair_fraction": pe / max(pa, 1),
                       "flop_per_eval": flop}
     out["kernels"] = kern
-    out["roofline"] = {"bound": "alu", "kernel": "em_bwd_kernel (dense)",
+    out["roofline"] = {"bound": "alu", "kernel": "em_bwd_cull_kernel",
                        "achieved": kern["backward"]["achieved"],
                        "peak": PEAK_FP32_VECTOR, "unit": "TFLOP/s",
                        "frac": kern["backward"]["frac"], "traffic": None}

@@ -19,8 +19,8 @@
 // is a fixed-order reduction (per thread in j order, a butterfly per wave,
 // waves in order, blocks in order), so results are bitwise reproducible.
 // The optimisation never synchronises with the host: each iteration's
-// kernels (two, or five for large sources) read a device "stopped" flag and return at once when the stage has
-// ended.
+// kernels (two, or five for large sources) read a device "stopped" flag and
+// return at once when the stage has ended.
 #pragma once
 
 #include <hip/hip_runtime.h>
