@@ -624,7 +624,8 @@ __global__ __launch_bounds__(kUpdThreads) void cond_prep_kernel(
   __shared__ double scratch[2 * kUpdThreads / 64];
   const int b = threadIdx.x;
   const bool act = b < K;
-  if (b == 0) *status = 0u;
+  __shared__ uint32_t bits;
+  if (b == 0) bits = 0u;
   __syncthreads();
   double cb = -INFINITY;
   float *q = cb_out + (size_t)b * kCond;
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(kUpdThreads) void cond_prep_kernel(
     for (int r = 0; r < 4; ++r)
       for (int c = 0; c <= r; ++c) C[tri(r, c)] = cov[16 * b + 4 * r + c];
     const double wb = w[b];
-    if (!(wb > 0.0) || !isfinite(wb)) set_status(status, kStBadArg);
+    if (!(wb > 0.0) || !isfinite(wb)) atomicOr(&bits, kStBadArg);
     if (chol_inv4(C, L, P)) {
       const double s = sqrt(0.5 * kLog2e);
       for (int j = 0; j < 3; ++j) q[j] = mu[4 * b + j];
@@ -652,11 +653,12 @@ __global__ __launch_bounds__(kUpdThreads) void cond_prep_kernel(
     } else {
       // a component that is not SPD takes no part (weight 2^-inf = 0)
       for (int j = 0; j < kCond; ++j) q[j] = 0.0f;
-      set_status(status, kStNotSpd);
+      atomicOr(&bits, kStNotSpd);
     }
   }
   double sdum = 0.0, mx = cb;
-  block_sum_max<kUpdThreads>(sdum, mx, scratch);
+  block_sum_max<kUpdThreads>(sdum, mx, scratch);   // (its barriers follow the bits)
+  if (b == 0) *status = bits;
   if (act) q[3] = isfinite(cb) ? (float)((cb - mx) * kLog2e) : -INFINITY;
 }
 
