@@ -729,7 +729,7 @@ __global__ void d2d_out_kernel(const State *st, double *T, int *counts) {
 // The state after the last step of an iteration (its kTrials x M rows in
 // vrows), or, for the first one of a stage, f at the stage's pose (M rows).
 // By kThreads threads, the result in *c (LDS); `hist` non-NULL in the one
-// block that keeps the history.
+// block that keeps the history.  Ends with a barrier on every path.
 __device__ inline void accept_step(State *st, int par, bool first,
                                    const double *__restrict__ vrows, int M, double *hist,
                                    int hist_len, Cur *c) {
@@ -742,9 +742,8 @@ __device__ inline void accept_step(State *st, int par, bool first,
   if (tid < (int)(sizeof(Cur) / sizeof(double))) reinterpret_cast<double *>(c)[tid] = cp[tid];
   const bool ended = !first && st->trial_stop;
   __syncthreads();
-  if (c->stopped) return;
-  if (ended) {
-    __syncthreads();
+  if (c->stopped || ended) {
+    __syncthreads();   // every wave has read the flag (the caller may write *c)
     if (tid == 0) c->stopped = 1;
     __syncthreads();
     return;
