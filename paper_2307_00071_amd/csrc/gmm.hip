@@ -289,8 +289,10 @@ bool make_bwd_cfg(int K, int64_t n, BwdCfg *out) {
 struct BwdCullCfg {
   int grid = 0;
   size_t lds = 0;
+  decltype(&em_bwd_cull_kernel<64, 8>) fn = nullptr;
 };
 constexpr int kBwdCullRows = 64;   // E rows kept
+constexpr int kBwdCullRunK = 40;   // from here on the dense kernel adds 8 points or more in float32
 
 bool pick_bwd_cull_cfg(int K, int64_t n, BwdCullCfg *out) {
   const char *off = getenv("GMM_CULL");
@@ -299,7 +301,9 @@ bool pick_bwd_cull_cfg(int K, int64_t n, BwdCullCfg *out) {
   if (di.cus <= 0 || K > kBwdCullBlock) return false;
   const size_t lds = bwd_cull_lds_bytes<kBwdCullRows>(K);
   if (lds > (di.lds_max ? di.lds_max : 65536)) return false;
-  const void *fn = reinterpret_cast<const void *>(&em_bwd_cull_kernel<kBwdCullRows>);
+  out->fn = K < kBwdCullRunK ? &em_bwd_cull_kernel<kBwdCullRows, 1>
+                             : &em_bwd_cull_kernel<kBwdCullRows, 8>;
+  const void *fn = reinterpret_cast<const void *>(out->fn);
   if (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                          (int)lds) != hipSuccess)
     return false;
@@ -2479,7 +2483,7 @@ gmm_status gmm_loglik_backward(const float *pts, int64_t n, const float *pose6,
   }
   for (int rep = 0; rep < (timed ? g_prof.reps : 1); ++rep) {
     if (cull)
-      hipLaunchKernelGGL(em_bwd_cull_kernel<kBwdCullRows>, dim3(bcc.grid), dim3(kBwdCullBlock),
+      hipLaunchKernelGGL(bcc.fn, dim3(bcc.grid), dim3(kBwdCullBlock),
                          bcc.lds, r.s, at<float4>(ws, r.L.pts4), at<float4>(ws, r.L.tsph),
                          at<float>(ws, r.L.cpar[r.cur]), at<float4>(ws, r.L.shift[r.cur]), Rt,
                          grad_L, at<double>(ws, r.L.part), g_pts, a, n);

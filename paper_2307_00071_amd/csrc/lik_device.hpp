@@ -10,6 +10,8 @@
 
 #include "em_device.hpp"
 
+#include <type_traits>
+
 namespace gmm_dev {
 
 // ------------------------------------------------------------ setup launch
@@ -185,7 +187,8 @@ __global__ __launch_bounds__(kLikFinishThreads) void lik_finish_kernel(
 //  normaliser wave 0: s_p, G_p over the waves, then g_p = dL/dy_p, dL/dx_p
 //             and the pose sums; meanwhile wave 1 + c lists chunk c of the
 //             next tile;
-//  M-phase    lanes = (slot, 8-point subset): N, A, B as the forward's;
+//  M-phase    lanes = (slot, 8-point subset): N, A, B as the forward's, float32
+//             over RUN points, then FP64;
 //  far points (s_p below 2^-100): maxima and sums, each wave over its share
 //             of all components, then a second M-phase over all components
 //             with the weights of the far points alone.  With one thread
@@ -246,7 +249,37 @@ struct PairSums {
   }
 };
 
-template <int SCAP>
+// Ten statistics summed in FP64 over the 8 adjacent lanes of a slot as a
+// reduce-scatter: half-mirror (q, 7 - q) keeps 0-4 in lanes 0-3 and 5-9 in
+// lanes 4-7 (h = 0, 5); q ^ 2 keeps h, h + 1 where bit 1 of q is clear and
+// h + 3, h + 4 where it is set; q ^ 1 the first or second of those.  *third:
+// h + 2, in every lane.  float32 values travel as such to the first sum.
+__device__ __forceinline__ double from_half_mirror(float v) {
+  return (double)dpp_from_half_mirror(v);
+}
+__device__ __forceinline__ double from_half_mirror(double v) { return dpp_f64<0x141>(v); }
+
+template <typename V>
+__device__ __forceinline__ double scatter8_f64(const V *a, int q, double *third) {
+  const bool hi = (q & 4) != 0, b2 = (q & 2) != 0, b1 = (q & 1) != 0;
+  double k[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    k[j] = (double)(hi ? a[j + 5] : a[j]) + from_half_mirror(hi ? a[j] : a[j + 5]);
+  }
+  const double v0 = (b2 ? k[3] : k[0]) + dpp_f64<0x4E>(b2 ? k[0] : k[3]);
+  const double v1 = (b2 ? k[4] : k[1]) + dpp_f64<0x4E>(b2 ? k[1] : k[4]);
+  const double v2 = k[2] + dpp_f64<0x4E>(k[2]);
+  *third = v2 + dpp_f64<0xB1>(v2);
+  return (b1 ? v1 : v0) + dpp_f64<0xB1>(b1 ? v0 : v1);
+}
+
+// RUN: points that a thread adds in float32 before they reach FP64.  The
+// dense kernel adds 1 (K <= 8) to 5 points in float32 below 40 components and
+// at least 8 from there on; this one adds no more.  (A sum of a slot's eight
+// lanes in float32 as well took the same time: 300,000 points, K = 200, all
+// components active 166 us a call, 100,000 with 40 % of them 89 us.)
+template <int SCAP, int RUN>
 __global__ __launch_bounds__(kBwdCullBlock)
 __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
     const float4 *__restrict__ pts, const float4 *__restrict__ box,
@@ -325,6 +358,7 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
   };
 
   // N, A, B of nloc slots (component comp(slot)) from the E rows and Xs
+  static_assert(P == 8 && TRIP % RUN == 0, "scatter8_f64; whole runs");
   const int q = tid % P;
   auto m_phase = [&](int nloc, auto comp) {
     for (int sl = tid / P; sl < nloc; sl += SLOTS) {
@@ -332,31 +366,38 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
       const float4 sh = shift[b];
       const float *Eb = E + sl * RS + q * (TRIP + 1);
       const float4 *Xb = Xs + q * (TRIP + 1);
-      float av[kNStat];
+      std::conditional_t<RUN == TRIP, float, double> av[kNStat];
 #pragma unroll
-      for (int j = 0; j < kNStat; ++j) av[j] = 0.0f;
+      for (int r = 0; r < TRIP; r += RUN) {
+        float f[kNStat];
 #pragma unroll
-      for (int j = 0; j < TRIP; ++j) {
-        const float4 xr = Xb[j];
-        const float gm = Eb[j] * xr.w;
-        const float d0 = xr.x - sh.x, d1 = xr.y - sh.y, d2 = xr.z - sh.z;
-        const float w0 = gm * d0, w1 = gm * d1, w2 = gm * d2;
-        av[0] += gm;
-        av[1] += w0; av[2] += w1; av[3] += w2;
-        av[4] = fmaf(w0, d0, av[4]);
-        av[5] = fmaf(w1, d0, av[5]);
-        av[6] = fmaf(w1, d1, av[6]);
-        av[7] = fmaf(w2, d0, av[7]);
-        av[8] = fmaf(w2, d1, av[8]);
-        av[9] = fmaf(w2, d2, av[9]);
+        for (int j = 0; j < kNStat; ++j) f[j] = 0.0f;
+#pragma unroll
+        for (int j = r; j < r + RUN; ++j) {
+          const float4 xr = Xb[j];
+          const float gm = Eb[j] * xr.w;
+          const float d0 = xr.x - sh.x, d1 = xr.y - sh.y, d2 = xr.z - sh.z;
+          const float w0 = gm * d0, w1 = gm * d1, w2 = gm * d2;
+          f[0] += gm;
+          f[1] += w0; f[2] += w1; f[3] += w2;
+          f[4] = fmaf(w0, d0, f[4]);
+          f[5] = fmaf(w1, d0, f[5]);
+          f[6] = fmaf(w1, d1, f[6]);
+          f[7] = fmaf(w2, d0, f[7]);
+          f[8] = fmaf(w2, d1, f[8]);
+          f[9] = fmaf(w2, d2, f[9]);
+          // (two points in flight: with all eight, 33 registers spill and a
+          // call takes 4 to 5 us more)
+          if (RUN == 1 || (j & 1)) __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < kNStat; ++j) av[j] = r ? av[j] + f[j] : f[j];
       }
-      subset_sum<P>(av);
-      float u0 = av[0];
-#pragma unroll
-      for (int j = 1; j < P; ++j) u0 = (q == j) ? av[j] : u0;
-      double *ab = acc + (size_t)b * kNStat;
-      ab[q] += (double)u0;
-      if (q < 2) ab[q + 8] += (double)(q == 0 ? av[8] : av[9]);
+      double third;
+      const double mine = scatter8_f64(av, q, &third);
+      double *ab = acc + (size_t)b * kNStat + (q >> 2) * 5;
+      ab[(q & 2) + (q >> 1 & 1) + (q & 1)] += mine;
+      if ((q & 3) == 0) ab[2] += third;
     }
   };
 
