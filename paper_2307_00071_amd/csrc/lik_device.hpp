@@ -499,6 +499,9 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < NW; ++j) mx = fmaxf(mx, reds[j * T + lane]);
+      // the other lanes' weights are 0, so their terms only have to be finite:
+      // at padding's position every term may be -inf, less a maximum of -inf
+      if (!fb) mx = 0.0f;
       __syncthreads();
       PairSums ps;
       for (int b = b_lo; b < b_hi; ++b) ps.add(cpar + (size_t)b * kParStride, x, mx);
