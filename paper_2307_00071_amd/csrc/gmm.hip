@@ -284,39 +284,6 @@ bool make_bwd_cfg(int K, int64_t n, BwdCfg *out) {
   return true;
 }
 
-// Launch configuration of the culled backward kernel (one wave per
-// 64-component chunk, so K <= 512).
-struct BwdCullCfg {
-  int grid = 0;
-  size_t lds = 0;
-  decltype(&em_bwd_cull_kernel<64, 8>) fn = nullptr;
-};
-constexpr int kBwdCullRows = 64;   // E rows kept
-constexpr int kBwdCullRunK = 40;   // from here on the dense kernel adds 8 points or more in float32
-
-bool pick_bwd_cull_cfg(int K, int64_t n, BwdCullCfg *out) {
-  const char *off = getenv("GMM_CULL");
-  if (off && off[0] == '0') return false;
-  DevInfo di = dev_info();
-  if (di.cus <= 0 || K > kBwdCullBlock) return false;
-  const size_t lds = bwd_cull_lds_bytes<kBwdCullRows>(K);
-  if (lds > (di.lds_max ? di.lds_max : 65536)) return false;
-  out->fn = K < kBwdCullRunK ? &em_bwd_cull_kernel<kBwdCullRows, 1>
-                             : &em_bwd_cull_kernel<kBwdCullRows, 8>;
-  const void *fn = reinterpret_cast<const void *>(out->fn);
-  if (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lds) != hipSuccess)
-    return false;
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBwdCullBlock, lds) !=
-          hipSuccess || per_cu <= 0)
-    return false;
-  const int64_t ntiles = (n + kBwdCullT - 1) / kBwdCullT;
-  out->grid = (int)std::min<int64_t>(ntiles, (int64_t)di.cus * per_cu);
-  out->lds = lds;
-  return true;
-}
-
 bool pick_bwd_cfg(int K, int64_t n, BwdCfg *out) {
   if (K <= 128 && make_bwd_cfg<512, 64>(K, n, out)) return true;
   return make_bwd_cfg<1024, 64>(K, n, out);
@@ -545,19 +512,28 @@ const char *const kCullName[kNumCull] = {
     "c1024t128r",  "c1024t128s32r", "c512t128p16r", "c1024t128s96r",
     "c1024t128s128r", "c1024t64r"};
 
+// The culled shape that GMM_TILE_SHAPE names, or -1.
+int forced_cull() {
+  const char *e = getenv("GMM_TILE_SHAPE");
+  for (int i = 0; e && i < kNumCull; ++i)
+    if (strcmp(e, kCullName[i]) == 0) return i;
+  return -1;
+}
+
 // Culling is on unless GMM_CULL=0 or GMM_TILE_SHAPE names a dense shape.
-bool pick_cull_cfg(int K, int64_t n, CullCfg *out) {
+bool cull_on() {
   const char *off = getenv("GMM_CULL");
   if (off && off[0] == '0') return false;
   const char *e = getenv("GMM_TILE_SHAPE");
-  if (e && *e) {
-    for (int i = 0; i < kNumCull; ++i)
-      if (strcmp(e, kCullName[i]) == 0) {
-        if (!kCull[i](K, n, out)) return false;
-        out->name = kCullName[i];
-        return true;
-      }
-    return false;
+  return !e || !*e || forced_cull() >= 0;
+}
+
+bool pick_cull_cfg(int K, int64_t n, CullCfg *out) {
+  if (!cull_on()) return false;
+  if (const int f = forced_cull(); f >= 0) {
+    if (!kCull[f](K, n, out)) return false;
+    out->name = kCullName[f];
+    return true;
   }
   // measured: subsets of 8 points up to K = 128, of 16 above (depth frame);
   // beyond K = 512 1024-thread blocks with the cull parameters in registers
@@ -571,6 +547,38 @@ bool pick_cull_cfg(int K, int64_t n, CullCfg *out) {
       return true;
     }
   return false;
+}
+
+// Launch configuration of the culled backward kernel (one wave per
+// 64-component chunk, so K <= 512).
+struct BwdCullCfg {
+  int grid = 0;
+  size_t lds = 0;
+  decltype(&em_bwd_cull_kernel<64, 8>) fn = nullptr;
+};
+constexpr int kBwdCullRows = 64;   // E rows kept
+constexpr int kBwdCullRunK = 40;   // from here on the dense kernel adds 8 points or more in float32
+
+bool pick_bwd_cull_cfg(int K, int64_t n, BwdCullCfg *out) {
+  if (!cull_on()) return false;
+  DevInfo di = dev_info();
+  if (di.cus <= 0 || K > kBwdCullBlock) return false;
+  const size_t lds = bwd_cull_lds_bytes<kBwdCullRows>(K);
+  if (lds > (di.lds_max ? di.lds_max : 65536)) return false;
+  out->fn = K < kBwdCullRunK ? &em_bwd_cull_kernel<kBwdCullRows, 1>
+                             : &em_bwd_cull_kernel<kBwdCullRows, 8>;
+  const void *fn = reinterpret_cast<const void *>(out->fn);
+  if (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds) != hipSuccess)
+    return false;
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBwdCullBlock, lds) !=
+          hipSuccess || per_cu <= 0)
+    return false;
+  const int64_t ntiles = (n + kBwdCullT - 1) / kBwdCullT;
+  out->grid = (int)std::min<int64_t>(ntiles, (int64_t)di.cus * per_cu);
+  out->lds = lds;
+  return true;
 }
 
 // GMM_DEBUG=1: the launch configuration of each fit on stderr.
