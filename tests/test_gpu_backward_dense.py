@@ -10,8 +10,7 @@ from tests.test_gpu_registration import _check, _registration_problem, _to
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,k", [(777, 1), (5000, 16), (20011, 64), (3000, 129), (3000, 300),
-                                 (20011, 512)])
+@pytest.mark.parametrize("n,k", [(777, 1), (5000, 16), (20011, 64), (3000, 129), (3000, 300)])
 def test_dense_kernel_matches_the_oracle(n, k, monkeypatch):
     print("case: dense backward n=%d k=%d" % (n, k), flush=True)
     monkeypatch.setenv("GMM_CULL", "0")
