@@ -18,6 +18,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include <atomic>
@@ -31,20 +32,39 @@ constexpr std::chrono::microseconds kPollLimit{1000};
 
 struct ReadPage {
   std::mutex mu;
-  bool tried = false;
+  uint32_t missed = 0;                    // failed or skipped attempts
   uint64_t *host = nullptr, *dev = nullptr;
   std::atomic<uint32_t> busy{0};          // bit per slot
   uint32_t seq[kReadSlots] = {};          // written by the slot's holder only
 };
 inline ReadPage g_read;
 
-inline bool read_page(bool may_alloc) {
+// GMM_READ_TEST (tests of each way): copy - the copy always; page - an error
+// where the page cannot be used; nopage - the page's allocation fails; refuse -
+// a launch that the runtime refuses.
+enum ReadTest { kReadAsIs, kReadCopy, kReadPageOnly, kReadNoPage, kReadRefuse };
+inline ReadTest read_test() {
+  const char *e = getenv("GMM_READ_TEST");
+  if (!e) return kReadAsIs;
+  const char *const names[] = {"", "copy", "page", "nopage", "refuse"};
+  for (int i = 1; i < 5; ++i)
+    if (strcmp(e, names[i]) == 0) return (ReadTest)i;
+  return kReadAsIs;
+}
+
+// An attempt that fails is repeated at the 2nd, 4th, 8th, ... call after it.
+// Another thread may be capturing a stream: in the relaxed mode the
+// allocation is allowed then and leaves that capture alone.
+inline bool read_page(bool may_alloc, ReadTest test) {
   std::lock_guard<std::mutex> lk(g_read.mu);
-  if (!g_read.host && !g_read.tried && may_alloc) {
-    g_read.tried = true;
+  if (g_read.host || !may_alloc) return g_read.host != nullptr;
+  if ((g_read.missed & (g_read.missed - 1)) == 0) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     void *h = nullptr, *d = nullptr;
     const size_t bytes = (size_t)kReadSlots * kReadWords * sizeof(uint64_t);
-    if (hipHostMalloc(&h, bytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
+    if (test != kReadNoPage &&
+        hipHostMalloc(&h, bytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
       if (hipHostGetDevicePointer(&d, h, 0) == hipSuccess && d) {
         memset(h, 0, bytes);
         g_read.dev = static_cast<uint64_t *>(d);
@@ -53,8 +73,10 @@ inline bool read_page(bool may_alloc) {
         (void)hipHostFree(h);
       }
     }
-    (void)hipGetLastError();
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!g_read.host) (void)hipGetLastError();
   }
+  if (!g_read.host) ++g_read.missed;
   return g_read.host != nullptr;
 }
 
@@ -78,10 +100,15 @@ inline hipError_t read_words_copy(const uint32_t *src, int n, void *out, hipStre
 inline hipError_t read_words(const void *src_, int n, void *out, hipStream_t s,
                              bool may_alloc = true) {
   const uint32_t *src = static_cast<const uint32_t *>(src_);
+  const ReadTest test = read_test();
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (n > kReadWords || hipStreamIsCapturing(s, &cap) != hipSuccess ||
-      cap != hipStreamCaptureStatusNone || !read_page(may_alloc))
-    return read_words_copy(src, n, out, s);
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusInvalidated;
+  }
+  if (n > kReadWords || cap != hipStreamCaptureStatusNone || test == kReadCopy ||
+      !read_page(may_alloc, test))
+    return test == kReadPageOnly ? hipErrorNotReady : read_words_copy(src, n, out, s);
   int slot = -1;
   for (uint32_t b = g_read.busy.load(); slot < 0;) {
     const uint32_t open = ~b & ((1u << kReadSlots) - 1u);
@@ -91,9 +118,16 @@ inline hipError_t read_words(const void *src_, int n, void *out, hipStream_t s,
   }
   uint64_t *h = g_read.host + (size_t)slot * kReadWords;
   const uint32_t seq = ++g_read.seq[slot];
-  hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(64), 0, s, src, n,
-                     g_read.dev + (size_t)slot * kReadWords, seq);
-  hipError_t e = hipGetLastError();
+  uint64_t *dst = g_read.dev + (size_t)slot * kReadWords;
+  void *args[] = {&src, &n, &dst, const_cast<uint32_t *>(&seq)};
+  hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&publish_kernel),
+                                 dim3(test == kReadRefuse ? 0 : 1),
+                                 dim3(64), args, 0, s);
+  if (e != hipSuccess) {   // refused: nothing will store to the slot
+    (void)hipGetLastError();
+    g_read.busy.fetch_and(~(1u << slot));
+    return read_words_copy(src, n, out, s);
+  }
   auto arrived = [&] {
     for (int i = 0; i < n; ++i) {
       const uint64_t v = __atomic_load_n(h + i, __ATOMIC_ACQUIRE);
@@ -103,7 +137,7 @@ inline hipError_t read_words(const void *src_, int n, void *out, hipStream_t s,
     return true;
   };
   bool ok = false;
-  if (e == hipSuccess) {
+  {
     const auto until = std::chrono::steady_clock::now() + kPollLimit;
     do {
       for (int k = 0; k < 64 && !(ok = arrived()); ++k) __builtin_ia32_pause();
