@@ -175,7 +175,7 @@ struct Reg {
 gmm_status reg_enqueue_fused(const Reg &r, const D2DLayout &L, hipStream_t s);
 
 gmm_status reg_enqueue(const Reg &r, const D2DLayout &L, hipStream_t s) {
-  if (r.m <= kFuseComp) return reg_enqueue_fused(r, L, s);
+  if (fused_iteration(r.m, r.n)) return reg_enqueue_fused(r, L, s);
   void *ws = r.ws;
   const int m = r.m, n = r.n;
   const float *w = r.w, *mu = r.mu, *cov = r.cov, *tw = r.tw, *tmu = r.tmu, *tcov = r.tcov;
@@ -210,7 +210,7 @@ gmm_status reg_enqueue(const Reg &r, const D2DLayout &L, hipStream_t s) {
   return GMM_OK;
 }
 
-// The same call, two launches an iteration (m <= kFuseComp).
+// The same call, two launches an iteration (fused_iteration).
 gmm_status reg_enqueue_fused(const Reg &r, const D2DLayout &L, hipStream_t s) {
   State *st = at<State>(r.ws, L.state);
   const Mix a = mix_of(r.ws, L.src, r.m), b = mix_of(r.ws, L.tgt, r.n);

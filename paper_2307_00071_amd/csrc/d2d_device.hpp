@@ -34,7 +34,9 @@ namespace d2d_dev {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kTrials = 8;          // step sizes 1, 1/2, ..., 2^-7
-constexpr int kFuseComp = 256;      // source components of the two-launch iteration
+// The two-launch iteration (fused_iteration below): source components, and
+// target components per source component.
+constexpr int kFuseLeast = 16, kFuseComp = 128, kFuseLong = 8;
 constexpr int kPose = 12;           // R row-major (9), t (3)
 constexpr int kNStat = 27;          // H: delta-delta 6, delta-t 9, t-t 6; grad 6
 constexpr double kIsoEps = 1e-3;
@@ -536,7 +538,7 @@ constexpr int kStepThreads = 1024;   // >= kNStat * kStepGroups
 
 // tot = the column sums, by kStepThreads threads (two barriers).
 // kHead rows of each group may come preloaded (`head`).
-constexpr int kHead = 7;   // covers M <= kFuseComp
+constexpr int kHead = 4;   // covers M <= kFuseComp
 static_assert(kStepThreads >= kNStat * kStepGroups, "a thread per group and column");
 static_assert(kHead * kStepGroups >= kFuseComp, "every row of a fused call");
 struct RowHead {
@@ -707,24 +709,33 @@ __global__ void d2d_out_kernel(const State *st, double *T, int *counts) {
 
 // ------------------------------------------------- two launches an iteration
 //
-// For a source of at most kFuseComp components an iteration is two launches
-// instead of five: every block first forms what it needs of the sums of the
-// launch before (the same bits in every block, block 0 writes them to the
-// state), then does its own source component:
+// Where fused_iteration() says so an iteration is two launches instead of
+// five: every block first forms what it needs of the sums of the launch before
+// (the same bits in every block, block 0 writes them to the state), then does
+// its own source component:
 //   d2d_it_stats_kernel  the accepted trial of the last step, then the 27
 //                        statistics at the new pose;
 //   d2d_it_step_kernel   the step and its trial poses, then the values at
 //                        all eight.
 // What is bound here is launches and short dependent FP64 chains, not
-// arithmetic (10^4 pairs at K = 100).  Five launches took 35.5 us an
-// iteration, and each dependent launch left after a stage has ended about
-// 4 us; two take 17-18 us (step and values 12: sums 3.5, 6 x 6 solve 1.7,
-// trial poses 1, values 3.3; accept and statistics 5.2) and 6.4 us when
-// there is nothing to do: 10 + 30 iterations at K = 100, 885 -> 581 us a
-// call.  The step's blocks come in pairs, four trials each, so that the FP64
-// work spreads over the chip (one block with two rounds of four: 6.5 us a
-// round).  Every block reads the rows of all M source components, M^2 x 43
-// doubles an iteration over the chip, so larger sources keep five launches.
+// arithmetic (10^4 pairs at K = 100).  Two launches take 17-18 us an
+// iteration (step and values 12: sums 3.5, 6 x 6 solve 1.7, trial poses 1,
+// values 3.3; accept and statistics 5.2) and 6.4 us when a stage has ended.
+//
+// The step's blocks have 1,024 threads and four trials each, two blocks a
+// source component: up to 128 components they are all resident on 256 CUs, a
+// round more costs more than the launches saved.  With few components they
+// hold few CUs, and long targets make that FP64 work the larger part.  The
+// accept looks at one trial after another, five launches at all of them at
+// once.  Measured, us a call, two launches against five:
+//   components   16 x 16 483, 494     64 x 64 467, 497     128 x 128 478, 523
+//   (5 + 15      16 x 128 474, 490    64 x 512 571, 592    128 x 1024 756, 840
+//   iterations)  16 x 512 578, 551    64 x 1024 740, 706   192 x 128 673, 575
+//                4 x 256 671, 504     8 x 1024 767, 660    256 x 256 723, 689
+//   (10 + 30)    100 x 100 665, 783   72 x 600 999, 1075   40 x 300 867, 906
+__host__ inline bool fused_iteration(int m, int n) {
+  return m >= kFuseLeast && m <= kFuseComp && n <= kFuseLong * m;
+}
 
 // The state after the last step of an iteration (its kTrials x M rows in
 // vrows), or, for the first one of a stage, f at the stage's pose (M rows).
