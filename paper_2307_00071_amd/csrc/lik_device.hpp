@@ -194,6 +194,20 @@ __global__ __launch_bounds__(kLikFinishThreads) void lik_finish_kernel(
 //             with the weights of the far points alone.  With one thread
 //             per far point walking the components twice, N = 100,000, K =
 //             200 with 14 % far points took 216 us a launch (38 us without).
+//
+// Against em_bwd_kernel (us a call): 300,000 points of an image 337 and 1,216
+// at K = 512, 150 and 375 at K = 200, 94 and 128 at K = 64; in random order 727
+// and 2,262, 290 and 665, 131 and 172.  The other side of the line: components
+// so wide that every pair is active and no point is far (sigma three times
+// that of a fit), 166 and 149 at K = 200, 380 and 270 at K = 512; at 100,000
+// points 97 and 99, 178 and 153.  There the dense kernel gains by 13 to 32
+// points a thread and by rows that it need not form twice.  It is not chosen
+// for them: on the host nothing tells such a call from a cloud in random
+// order, every box of which is as active; a choice on the device, by sampled
+// boxes, took 7 us more in every call and the dense kernel for those clouds.
+// More rows cost blocks per CU: 128 of them 225 us instead of 164 at 100,000
+// points, K = 512, all of them in blocks of 1,024 threads 96 instead of 90 at
+// K = 200.
 constexpr int kBwdCullT = 64;
 constexpr int kBwdCullBlock = 512;
 constexpr int kBwdCullP = 8;                        // point subsets per slot
