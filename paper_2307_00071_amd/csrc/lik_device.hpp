@@ -220,7 +220,7 @@ __host__ __device__ constexpr size_t bwd_cull_lds_bytes(int K) {
   constexpr int NW = kBwdCullBlock / 64;
   return (((size_t)SCAP * kBwdCullRow * sizeof(float) + 15) & ~(size_t)15) +
          (size_t)kBwdCullXs * sizeof(float4) + (size_t)K * kNStat * sizeof(double) +
-         32 * sizeof(uint64_t) + 7 * kBwdCullT * sizeof(double) +
+         32 * sizeof(uint64_t) + 6 * kBwdCullT * sizeof(double) +
          (size_t)4 * NW * kBwdCullT * sizeof(float) + (size_t)2 * K * sizeof(uint16_t) +
          4 * sizeof(int);
 }
@@ -309,8 +309,8 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
       smem + (((size_t)SCAP * RS * sizeof(float) + 15) & ~(size_t)15));
   double *acc = reinterpret_cast<double *>(Xs + kBwdCullXs);
   uint64_t *masks = reinterpret_cast<uint64_t *>(acc + (size_t)K * kNStat);  // 2 x 16
-  double *pgs = reinterpret_cast<double *>(masks + 32);    // 7 x T: lse and pose sums
-  float *reds = reinterpret_cast<float *>(pgs + 7 * T);     // 4 x NW x T
+  double *pgs = reinterpret_cast<double *>(masks + 32);    // 6 x T: pose sums
+  float *reds = reinterpret_cast<float *>(pgs + 6 * T);     // 4 x NW x T
   uint16_t *list = reinterpret_cast<uint16_t *>(reds + 4 * NW * T);   // 2 x K
   int *nact_s = reinterpret_cast<int *>(list + 2 * K);                // 2
   __shared__ uint64_t fbmask;
@@ -319,20 +319,17 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nchk = (K + 63) >> 6;   // <= NW
   const int tx = lane + lane / TRIP;
-  const double Cb = *reinterpret_cast<const double *>(cpar + (size_t)K * kParStride);
   const float inv_s2 = (float)(2.0 / kLog2e);
   const float gl = grad_L ? (float)grad_L[0] : 1.0f;
   for (int i = tid; i < K * kNStat; i += BLOCK) acc[i] = 0.0;
   const CullPar creg = cull_par(cpar, K, (w << 6) + lane);
-  for (int i = tid; i < 7 * T; i += BLOCK) pgs[i] = 0.0;
+  for (int i = tid; i < 6 * T; i += BLOCK) pgs[i] = 0.0;
   unsigned long long npairs = 0;
 
   // wave 0: dL/dx of this lane's point from s_p and G_p, and its share of
-  // the log-likelihood and the pose sums
-  auto finish_point = [&](float4 x, size_t idx, float st, float mref, float H0, float H1,
-                          float H2) {
+  // the pose sums
+  auto finish_point = [&](float4 x, size_t idx, float st, float H0, float H1, float H2) {
     const float r = 1.0f / st;
-    pgs[lane] += (Cb + (double)mref + (double)log2f(st)) * kLn2;
     const float c = -r * inv_s2;
     const float g0 = c * H0, g1 = c * H1, g2 = c * H2;
     float tv0 = 0.0f, tv1 = 0.0f, tv2 = 0.0f;
@@ -349,7 +346,7 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
       g_pts[3 * idx + 2] = gl * o2;
     }
     const float rx = x.x - tv0, ry = x.y - tv1, rz = x.z - tv2;
-    double *pg = pgs + T + lane;
+    double *pg = pgs + lane;
     pg[0] += g0; pg[T] += g1; pg[2 * T] += g2;
     pg[3 * T] += (double)(ry * g2 - rz * g1);
     pg[4 * T] += (double)(rz * g0 - rx * g2);
@@ -479,7 +476,7 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
       const uint64_t fm = __ballot(fb);
       if (lane == 0) fbmask = fm;
       if (valid && !fb)
-        finish_point(x, (size_t)tile * T + lane, ps.s, 0.0f, ps.G0, ps.G1, ps.G2);
+        finish_point(x, (size_t)tile * T + lane, ps.s, ps.G0, ps.G1, ps.G2);
     }
     if (more) build_list(nxt);
     __syncthreads();                                              // B
@@ -524,7 +521,7 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
       if (w == 0) {
         ps.load(reds, lane);
         Xs[tx] = make_float4(x.x, x.y, x.z, fb ? 1.0f / ps.s : 0.0f);
-        if (fb) finish_point(x, (size_t)tile * T + lane, ps.s, mx, ps.G0, ps.G1, ps.G2);
+        if (fb) finish_point(x, (size_t)tile * T + lane, ps.s, ps.G0, ps.G1, ps.G2);
       }
       for (int c0 = 0; c0 < K; c0 += SCAP) {
         const int nloc = min(SCAP, K - c0);
@@ -543,9 +540,9 @@ __attribute__((amdgpu_waves_per_eu(6, 8))) void em_bwd_cull_kernel(
   // ---- this block's partial row
   double *row = part + (size_t)blockIdx.x * a.ncols;
   for (int i = tid; i < K * kNStat; i += BLOCK) row[i] = acc[i];   // component-major
-  if (w < 7) {
+  if (w < kBwdExtra) {   // (the log-likelihood column before them is not used)
     const double v = wave_sum_f64(pgs[w * T + lane]);
-    if (lane == 0) row[kNStat * K + w] = v;
+    if (lane == 0) row[kNStat * K + 1 + w] = v;
   }
   if (tid == 0 && a.pairs) atomicAdd(a.pairs, npairs);
 }
