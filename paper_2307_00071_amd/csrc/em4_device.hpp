@@ -675,23 +675,36 @@ __device__ __forceinline__ float cond_logterm(const float *__restrict__ q, float
 }
 
 // beta_b = softmax of the marginal log terms, E = sum beta m_b,
-// V = sum beta (v_b + (m_b - E)^2), with FP64 sums.  A block has 64 locations
-// and kCondWaves waves, each with a range of the components; the sums of the
-// ranges are added in wave order.  Bound by the latency of the components'
-// scalar loads: 10 us at an image's 76,800 locations, K = 100; 38 us with a
-// thread per location (one wave a SIMD).
+// V = sum beta (v_b + (m_b - E)^2), with FP64 sums.  A group of 64 locations
+// belongs to SPLIT waves of a block of kCondWaves, each with a range of the
+// components; the sums of the ranges are added in wave order.  Bound by the
+// latency of the components' scalar loads where locations are few (76,800 of an
+// image, K = 100: 10 us with four waves a group, 38 with one) and by the
+// exchange of the sums where they are many.
 constexpr int kCondWaves = 4;
 constexpr int64_t kCondBlocks = 1 << 20;   // then blocks take several groups
 
+// Four waves a group until the groups themselves fill the chip: us a call with
+// one and four waves a group, K = 4: 32.0 and 31.8 at 150,000 locations, 32.2
+// and 33.5 at 307,200, 40.8 and 59.3 at 2,000,000; K = 32: 38.1 and 34.2, 39.6 and
+// 38.6, 77.3 and 88.4; K = 128: 60.1 and 44.8, 68.1 and 57.9, 198.5 and 197.4.
+constexpr int64_t kCondPerComp = 16384;
+__host__ inline bool cond_split(int64_t m, int K) { return m < K * kCondPerComp; }
+
+template <int SPLIT>
 __global__ __launch_bounds__(64 * kCondWaves) void cond4_kernel(
     const float *__restrict__ locs, int64_t M, const float *__restrict__ cb, int K,
     float *__restrict__ Eout, float *__restrict__ Vout, uint32_t *status) {
-  __shared__ double sums[kCondWaves][3][64];
-  __shared__ float top[kCondWaves][64];
+  constexpr int GROUPS = kCondWaves / SPLIT;   // of a block at a time
+  static_assert(SPLIT == 1 || SPLIT == kCondWaves, "a group's waves are a whole block");
+  __shared__ double sums[SPLIT][3][64];
+  __shared__ float top[SPLIT][64];
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lo = (w * K) / kCondWaves, hi = ((w + 1) * K) / kCondWaves;
-  for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < M; i0 += (int64_t)gridDim.x * 64) {
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = SPLIT == 1 ? 0 : wv;
+  const int lo = (w * K) / SPLIT, hi = ((w + 1) * K) / SPLIT;
+  const int64_t g0 = (int64_t)blockIdx.x * GROUPS + (SPLIT == 1 ? wv : 0);
+  for (int64_t i0 = g0 * 64; i0 < M; i0 += (int64_t)gridDim.x * GROUPS * 64) {
     const int64_t i = i0 + lane;
     float x = 0.0f, y = 0.0f, z = 0.0f;
     if (i < M) {
@@ -714,29 +727,33 @@ __global__ __launch_bounds__(64 * kCondWaves) void cond4_kernel(
         s1 += e * (double)m;
         s2 = fma(e, (double)q[14] + (double)m * (double)m, s2);
       }
-      sums[w][0][lane] = s;
-      sums[w][1][lane] = s1;
-      sums[w][2][lane] = s2;
-      __syncthreads();
-      s = sums[0][0][lane]; s1 = sums[0][1][lane]; s2 = sums[0][2][lane];
+      if constexpr (SPLIT > 1) {
+        sums[w][0][lane] = s;
+        sums[w][1][lane] = s1;
+        sums[w][2][lane] = s2;
+        __syncthreads();
+        s = sums[0][0][lane]; s1 = sums[0][1][lane]; s2 = sums[0][2][lane];
 #pragma unroll
-      for (int v = 1; v < kCondWaves; ++v) {
-        s += sums[v][0][lane];
-        s1 += sums[v][1][lane];
-        s2 += sums[v][2][lane];
+        for (int v = 1; v < SPLIT; ++v) {
+          s += sums[v][0][lane];
+          s1 += sums[v][1][lane];
+          s2 += sums[v][2][lane];
+        }
       }
       // far from every component: redo with this location's own maximum
       const bool far = pass == 0 && i < M && fin && !(s >= 0x1p-100);
-      if (__ballot(far) == 0ull) break;   // the same locations in every wave
+      if (__ballot(far) == 0ull) break;   // the same locations in every wave of the group
       float mx = -INFINITY;
       for (int b = lo; b < hi; ++b) {
         float m;
         mx = fmaxf(mx, cond_logterm(cb + (size_t)b * kCond, x, y, z, m));
       }
-      top[w][lane] = mx;
-      __syncthreads();
+      if constexpr (SPLIT > 1) {
+        top[w][lane] = mx;
+        __syncthreads();
 #pragma unroll
-      for (int v = 0; v < kCondWaves; ++v) mx = fmaxf(mx, top[v][lane]);
+        for (int v = 0; v < SPLIT; ++v) mx = fmaxf(mx, top[v][lane]);
+      }
       if (far) shift = mx;
     }
     if (w == 0 && i < M) {
@@ -754,7 +771,7 @@ __global__ __launch_bounds__(64 * kCondWaves) void cond4_kernel(
         Vout[i] = NAN;
       }
     }
-    __syncthreads();   // the sums are read
+    if constexpr (SPLIT > 1) __syncthreads();   // the sums are read
   }
 }
 

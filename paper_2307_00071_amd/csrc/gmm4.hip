@@ -596,7 +596,10 @@ gmm_status gmm4_color_conditional(const float *locs, int64_t m, int32_t k, const
   hipLaunchKernelGGL(cond_prep_kernel, dim3(1), dim3(kUpdThreads), 0, s, w, mu, cov, k, cb,
                      status);
   HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(cond4_kernel, dim3((unsigned)std::min((m + 63) / 64, kCondBlocks)),
+  const bool split = cond_split(m, k);
+  const int64_t per = split ? 64 : 64 * kCondWaves;   // locations of a block
+  hipLaunchKernelGGL(split ? cond4_kernel<kCondWaves> : cond4_kernel<1>,
+                     dim3((unsigned)std::min((m + per - 1) / per, kCondBlocks)),
                      dim3(64 * kCondWaves), 0, s, locs, m, cb, k, expected, variance, status);
   HIP_TRY(hipGetLastError());
   return GMM_OK;
