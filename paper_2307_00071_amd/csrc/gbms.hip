@@ -214,7 +214,8 @@ gmm_status run_meanshift(const MsLayout &L, void *ws, hipStream_t s, const float
   // ---- every seed to its mode (at most n seeds; the count is on the
   // device): one wave per seed, or a block per seed when there are at most
   // thr seeds; each kernel returns at once when the other one applies.
-  // GMM_MS_SEED_WAVES=1|4 forces one form (tests of both on one input).
+  // GMM_MS_SEED_WAVES=1|4 forces one form, 1 the wave per seed, 4 the block (of
+  // kMsSeedWaves waves) per seed (tests of both on one input).
   int thr = kMsBlockSeeds;
   if (const char *e = getenv("GMM_MS_SEED_WAVES")) {
     if (e[0] == '1') thr = 0;

@@ -686,7 +686,7 @@ gmm_status status_from_bits(uint32_t bits) {
   if (bits & kStBadArg) return fail(GMM_ERR_INVALID_ARG, "device: invalid label or parameter");
   if (bits & kStNotSpd) return fail(GMM_ERR_NOT_SPD, "device: covariance not SPD");
   if (bits & kStNonFinite) return fail(GMM_ERR_NONFINITE, "device: non-finite value");
-  if (bits & kStDevice) return fail(GMM_ERR_DEVICE, "device: the one-launch fit's grid barrier gave up");
+  if (bits & kStDevice) return fail(GMM_ERR_DEVICE, "device: the one-launch fit's exchange between its blocks gave up");
   return GMM_OK;
 }
 
