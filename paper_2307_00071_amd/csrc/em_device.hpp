@@ -1612,10 +1612,7 @@ __device__ __forceinline__ void cull_end(const CullLds &L, double *__restrict__ 
 // list of a tile is the set of its labels), a separate instantiation so
 // that the soft passes carry none of its code.  MEANS: a soft pass that
 // accumulates N and S1 only (the first pass of two-pass moments; the
-// second-moment columns stay zero).  Log-likelihood passes are em_lik_kernel's,
-// so lse_out is NULL here; without the parameter the compiler's registers for
-// 1,024-thread blocks fall from 98 to 79 and a LiDAR fit (2,000,000 points,
-// K = 1000, 20 iterations) takes 14.8 ms instead of 14.6.
+// second-moment columns stay zero).
 template <int BLOCK, int T, int TRIP, int SCAP, bool CPR, bool LAB, bool MEANS>
 __global__ __launch_bounds__(BLOCK)
 __attribute__((amdgpu_waves_per_eu(GMM_CULL_WPE, 8))) void em_cull_kernel(

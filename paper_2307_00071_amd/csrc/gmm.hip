@@ -437,6 +437,10 @@ void launch_lik(const CullCfg &c, hipStream_t s, const float4 *pts, const float4
                      pts, sph, cpar, part, lse, a);
 }
 
+// (Log-likelihood passes are em_lik_kernel's, so lse is NULL here.  Without that
+// parameter the compiler's registers for 1,024-thread blocks fall from 98 to 79
+// and a LiDAR fit, 2,000,000 points, K = 1000, 20 iterations, takes 14.8 ms
+// instead of 14.6.)
 template <int BLOCK, int T, int TRIP, int SCAP, bool CPR, bool LAB, bool MEANS>
 void launch_cull(const CullCfg &c, hipStream_t s, const float4 *pts,
                  const float4 *sph, const float *cpar, const float4 *shift,
